@@ -375,15 +375,33 @@ __device__ __forceinline__ void collide(R (&f)[9], const R omega, const R gx, co
 // Written with the normal as a runtime value and every population index a
 // compile-time constant (the roles of the directions become predicates), so
 // that the populations stay in registers.
+// open_values gives the two boundary values in the compute type, as the rebuild
+// uses them: (u.n, u.t) of a velocity node, (rho, 0) (deviations: (rho - 1, 0))
+// of a pressure node.
 template <class R, bool SHIFT>
-__device__ __forceinline__ void apply_open(R (&f)[9], unsigned b, const double *__restrict__ v)
+__device__ __forceinline__ void open_values(unsigned b, double v0, double v1, R &p, R &q)
 {
     const unsigned k = (b - 1u) & 3u;  // normal +x, -x, +y, -y
     const int nxn = k == 0 ? 1 : (k == 1 ? -1 : 0);
     const int nyn = k == 2 ? 1 : (k == 3 ? -1 : 0);
     const int tx = -nyn, ty = nxn;
+    if (b <= 4u) {
+        p = (R)(v0 * nxn + v1 * nyn);
+        q = (R)(v0 * tx + v1 * ty);
+    } else {
+        p = SHIFT ? (R)(v0 - 1.0) : (R)v0;
+        q = R(0);
+    }
+}
+
+template <class R, bool SHIFT>
+__device__ __forceinline__ void apply_open_values(R (&f)[9], unsigned b, R p, R q)
+{
+    const unsigned k = (b - 1u) & 3u;
+    const int nxn = k == 0 ? 1 : (k == 1 ? -1 : 0);
+    const int nyn = k == 2 ? 1 : (k == 3 ? -1 : 0);
+    const int tx = -nyn, ty = nxn;
     const bool velocity = b <= 4u;
-    const double v0 = v[0], v1 = v[1];
     R par = R(0), outg = R(0), tsum = R(0);
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -396,18 +414,17 @@ __device__ __forceinline__ void apply_open(R (&f)[9], unsigned b, const double *
     const R S = par + R(2) * outg;
     R run, rut;  // rho u.n, rho u.t
     if (velocity) {
-        const R un = (R)(v0 * nxn + v1 * nyn), ut = (R)(v0 * tx + v1 * ty);
         if constexpr (SHIFT) {
-            const R drho = (S + un) / (R(1) - un);
-            run = un + drho * un;
-            rut = ut + drho * ut;
+            const R drho = (S + p) / (R(1) - p);
+            run = p + drho * p;
+            rut = q + drho * q;
         } else {
-            const R rho = S / (R(1) - un);
-            run = rho * un;
-            rut = rho * ut;
+            const R rho = S / (R(1) - p);
+            run = rho * p;
+            rut = rho * q;
         }
     } else {
-        run = SHIFT ? (R)(v0 - 1.0) - S : (R)v0 - S;
+        run = p - S;
         rut = R(0);
     }
     const R tang = R(0.5) * (rut - tsum);
@@ -424,6 +441,14 @@ __device__ __forceinline__ void apply_open(R (&f)[9], unsigned b, const double *
 #pragma unroll
     for (int i = 0; i < 9; ++i)
         f[i] = g[i];
+}
+
+template <class R, bool SHIFT>
+__device__ __forceinline__ void apply_open(R (&f)[9], unsigned b, const double *__restrict__ v)
+{
+    R p, q;
+    open_values<R, SHIFT>(b, v[0], v[1], p, q);
+    apply_open_values<R, SHIFT>(f, b, p, q);
 }
 
 __device__ __forceinline__ void moments(const double (&f)[9], double gx, double gy, double alpha,

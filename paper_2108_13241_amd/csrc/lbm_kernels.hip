@@ -10,9 +10,9 @@
 // Offsets inside one lattice are 32-bit element indices (the runtime checks
 // 9 * nodes < 2^32).  The indirect layout's neighbours use the compact
 // row-rank description of lbm_plan.h (6 bytes per node).
+#include "lbm_dense.h"
 #include "lbm_device.h"
 #include "lbm_launch.h"
-
 
 namespace lbm {
 namespace {
@@ -112,38 +112,6 @@ __device__ __forceinline__ unsigned indirect_offsets(const uint32_t *__restrict_
     for (int i = 0; i < 9; ++i)
         nb[i] = list_base(src[i]);
     return sm;
-}
-
-// ------------------------------------------------------------ lane moves --
-// DPP move with control word CTRL; a lane whose source lane is outside its row
-// or wavefront keeps `edge` (the DPP "old" operand with bound_ctrl off), so the
-// end lanes need no select or branch.  Source lanes must be active.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v, uint32_t edge)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)v, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v, float edge)
-{
-    return __builtin_bit_cast(float, dpp_u32<CTRL>(__builtin_bit_cast(uint32_t, v),
-                                                   __builtin_bit_cast(uint32_t, edge)));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v, double edge)
-{
-    const uint64_t b = __builtin_bit_cast(uint64_t, v), e = __builtin_bit_cast(uint64_t, edge);
-    const uint32_t lo = dpp_u32<CTRL>((uint32_t)b, (uint32_t)e);
-    const uint32_t hi = dpp_u32<CTRL>((uint32_t)(b >> 32), (uint32_t)(e >> 32));
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-constexpr int kWaveShr1 = 0x138, kWaveShl1 = 0x130;
-// Wave-wide shift by one lane of a full wavefront: UP, lane l receives lane
-// l - 1's value (lane 0 keeps edge), else lane l + 1's (lane 63 keeps edge).
-template <bool UP, class R>
-__device__ __forceinline__ R lane_shift(R v, R edge)
-{
-    return dpp_move<UP ? kWaveShr1 : kWaveShl1>(v, edge);
 }
 
 // ---------------------------------------------------------------- gathers --
@@ -287,29 +255,6 @@ __device__ __forceinline__ void dense_pull_aligned(const typename ST::mem *__res
 }
 
 // ------------------------------------------------------------- step: dense --
-// Physics variant of a step kernel: plain BGK (no body force, no drag), body
-// force, or body force with a drag field; plus kOpen when the lattice has
-// open-boundary nodes (lattices without them run kernels free of that branch);
-// plus kTRT / kMRT for the two- / multiple-relaxation-time collisions.
-enum Phys : int { kBGK = 0, kForced = 1, kDragged = 2, kOpenBC = 4, kTRT = 8, kMRT = 16 };
-
-// Arguments shared by the dense A-B step kernels.
-template <class ST>
-struct DenseArgs {
-    const typename ST::mem *__restrict__ src;
-    typename ST::mem *__restrict__ dst;
-    const uint8_t *__restrict__ type;
-    const uint8_t *__restrict__ nmask;
-    const uint32_t *__restrict__ seg_interior;
-    const float *__restrict__ alpha;
-    const double *__restrict__ bc_val;
-    int nx, ny, pitch;
-    uint32_t bpr, nblocks;
-    typename ST::real omega, gx, gy;
-    Rates<typename ST::real> rt;
-    int fullway;
-};
-
 // Collision and streaming stores of one dense node (post-collision values to
 // the node's own slots of dst).
 template <class ST, int PH>
@@ -1540,6 +1485,29 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
     case kF32: return step_typed<F32>(s, t, cur);
     case kF16S: return step_typed<F16S>(s, t, cur);
     case kBF16S: return step_typed<BF16S>(s, t, cur);
+    }
+    return hipErrorInvalidValue;
+}
+
+int max_fused_steps(const DevState &s)
+{
+    // the full-way rule reads the state of two steps back from the other lattice
+    if (s.layout != kDenseAB || s.fullway)
+        return 1;
+    // StepsShape::kMax
+    const bool force = s.gx != 0.0 || s.gy != 0.0;
+    return s.mrt || s.open || s.alpha || (s.trt && force) ? 6 : 8;
+}
+
+hipError_t launch_steps(const DevState &s, int cur, int steps)
+{
+    if (steps < 2 || steps > max_fused_steps(s))
+        return hipErrorInvalidValue;
+    switch (s.dtype) {
+    case kF64: return launch_steps_f64(s, cur, steps);
+    case kF32: return launch_steps_f32(s, cur, steps);
+    case kF16S: return launch_steps_f16(s, cur, steps);
+    case kBF16S: return launch_steps_bf16(s, cur, steps);
     }
     return hipErrorInvalidValue;
 }

@@ -70,6 +70,16 @@ int64_t reduction_capacity(const DevState &s);
 // even or odd kernel).
 hipError_t launch_step(const DevState &s, int64_t t, int cur);
 
+// Most steps one launch_steps call takes (1: this lattice runs single steps only).
+int max_fused_steps(const DevState &s);
+// `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in
+// one launch (DENSE_AB), bitwise those of `steps` launch_step calls.
+hipError_t launch_steps(const DevState &s, int cur, int steps);
+hipError_t launch_steps_f64(const DevState &s, int cur, int steps);
+hipError_t launch_steps_f32(const DevState &s, int cur, int steps);
+hipError_t launch_steps_f16(const DevState &s, int cur, int steps);
+hipError_t launch_steps_bf16(const DevState &s, int cur, int steps);
+
 // Canonical populations fc (device FP64 [9][ny][pitch]) -> stored state at step t.
 // Full-way rule: fc's wall slots become the populations in flight; with
 // fill_walls they are taken instead from the fluid node each slot is fed by

@@ -712,15 +712,34 @@ static int32_t graph_length(const lbm_ctx *c)
     return bytes < 128.0 * (1 << 20) ? 32 : 0;
 }
 
-// Launch one step and advance the counters.
-static hipError_t step_once(lbm_ctx *c, hipStream_t stream)
+// Launch the next `steps` steps (one kernel; steps > 1 only where the layout has
+// the fused kernel) and advance the counters.
+static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
 {
     lbm::DevState s = c->s;
     s.stream = stream;
-    hipError_t e = lbm::launch_step(s, c->t, c->cur);
+    hipError_t e = steps > 1 ? lbm::launch_steps(s, c->cur, steps) : lbm::launch_step(s, c->t, c->cur);
     if (c->s.layout != LBM_DENSE_AA)
         c->cur ^= 1;
-    ++c->t;
+    c->t += steps;
+    return e;
+}
+
+// Launch n steps in as few launches as the fused kernel allows (an even number
+// of launches if `even`: the state then returns to the lattice it started from),
+// of equal length as nearly as possible.
+static hipError_t step_groups(lbm_ctx *c, hipStream_t stream, int64_t n, bool even)
+{
+    const int64_t kmax = lbm::max_fused_steps(c->s);
+    int64_t left = (n + kmax - 1) / kmax;
+    if (even && (left & 1) && left < n)
+        ++left;
+    hipError_t e = hipSuccess;
+    for (; left > 0 && e == hipSuccess; --left) {
+        const int64_t steps = (n + left - 1) / left;
+        e = step_group(c, stream, (int)steps);
+        n -= steps;
+    }
     return e;
 }
 
@@ -734,9 +753,9 @@ static int capture_graph(lbm_ctx *c, int key, int32_t G)
     const int cur0 = c->cur;
     hipGraph_t graph = nullptr;
     LBM_HIP(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = hipSuccess;
-    for (int32_t k = 0; k < G && e == hipSuccess; ++k)
-        e = step_once(c, c->capture_stream);
+    // G is even and so is the number of launches: a replay returns to the parity
+    // it started from
+    hipError_t e = step_groups(c, c->capture_stream, G, true);
     hipError_t e2 = hipStreamEndCapture(c->capture_stream, &graph);
     c->t = t0;
     c->cur = cur0;
@@ -782,8 +801,7 @@ int lbm_step(lbm_ctx *c, int64_t n)
         c->t += G;
         n -= G;
     }
-    for (int64_t k = 0; k < n; ++k)
-        LBM_HIP(c, step_once(c, c->s.stream));
+    LBM_HIP(c, step_groups(c, c->s.stream, n, false));
     return LBM_OK;
 }
 

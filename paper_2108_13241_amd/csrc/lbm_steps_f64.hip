@@ -1,0 +1,11 @@
+// k_steps for FP64 storage (one file per storage type: they compile in parallel).
+#include "lbm_multistep.h"
+
+namespace lbm {
+
+hipError_t launch_steps_f64(const DevState &s, int cur, int steps)
+{
+    return steps_typed<F64>(s, cur, steps);
+}
+
+}  // namespace lbm

@@ -1,0 +1,111 @@
+"""Several steps per launch (dense A-B) give bitwise the state of as many single steps.
+
+A call of one step runs the single-step kernels, which the other tests pin to the oracle; a
+call of n > 1 steps runs the fused kernel.  Sizes sit at the edges of its strips (48, 56, 112
+and 120 columns), below one strip and one row, and above several strips; step counts cover
+every number of steps per launch and uneven splits.
+"""
+import numpy as np
+import pytest
+
+from gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [(1, 1), (5, 3), (48, 17), (57, 2), (111, 9), (112, 40), (113, 33), (241, 26), (500, 75)]
+DTYPES = ["f64", "f32", "f16s", "bf16s"]
+
+
+def _lattice(nx, ny, dtype, variant, seed):
+    import paper_2108_13241_amd as lbm
+    import synthetic
+    kinds = variant.split("+")
+    walls = "solid" in kinds
+    m = (synthetic.random_mask(nx, ny, seed=seed, solid_fraction=0.15, walls=ny > 4)
+         if walls else synthetic.all_fluid(nx, ny))
+    g = (2e-4, -1e-4) if "force" in kinds or "drag" in kinds else (0.0, 0.0)
+    lat = lbm.Lattice(m, 0.7, force=g, dtype=dtype, layout="dense_ab")
+    rng = np.random.default_rng(seed)
+    if "drag" in kinds:
+        lat.set_porosity(rng.random((ny, nx)).astype(np.float32))
+    if "open" in kinds:
+        bc = np.zeros((ny, nx), dtype=np.uint8)
+        val = np.zeros((2, ny, nx))
+        bc[:, 0], bc[:, -1] = 5, 6
+        if ny > 2:
+            bc[-1, 1:-1] = 4
+        bc[m != 0] = 0
+        val[0] = np.where(bc >= 5, 1.0 + 0.01 * rng.random((ny, nx)), 0.02)
+        lat.set_boundaries(bc, val)
+    if "trt" in kinds:
+        lat.set_trt(3.0 / 16.0)
+    if "mrt" in kinds:
+        lat.set_mrt((1.64, 1.54, 1.9))
+    lat.init_equilibrium(*synthetic.random_fields(nx, ny, seed=seed + 1, u_amp=0.03))
+    return lat, m
+
+
+def _check(nx, ny, dtype, variant, counts, seed=11):
+    announce(f"fused steps {nx}x{ny} {dtype} {variant} {counts}")
+    fused, m = _lattice(nx, ny, dtype, variant, seed)
+    single, _ = _lattice(nx, ny, dtype, variant, seed)
+    for n in counts:
+        fused.step(n)
+        for _ in range(n):
+            single.step(1)
+        a, b = fused.get_populations(), single.get_populations()
+        assert np.isfinite(b[:, m == 0]).all()
+        assert np.array_equal(a, b), (n, np.abs(a - b).max())
+    fused.close()
+    single.close()
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("nx,ny", SIZES)
+def test_sizes(nx, ny, dtype):
+    _check(nx, ny, dtype, "solid+force", [2, 8, 5])
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("variant", ["", "trt", "mrt", "force", "solid", "solid+trt+force",
+                                     "solid+mrt+force", "solid+drag", "solid+drag+trt",
+                                     "solid+drag+mrt", "open", "open+trt", "open+mrt+force",
+                                     "open+solid+drag+mrt"])
+def test_variants(variant, dtype):
+    _check(131, 37, dtype, variant, [7, 9])
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_step_counts(dtype):
+    _check(150, 50, dtype, "solid", list(range(1, 18)))
+
+
+@pytest.mark.parametrize("graph", [0, 2, 10, 34])
+def test_graph_lengths(graph):
+    """Replays of any even length return to the lattice they start from."""
+    announce(f"fused steps, graphs of {graph}")
+    fused, _ = _lattice(200, 60, "f32", "solid+force", 5)
+    single, _ = _lattice(200, 60, "f32", "solid+force", 5)
+    fused.set_graph_steps(graph)
+    for n in (35, 1, 69):
+        fused.step(n)
+        for _ in range(n):
+            single.step(1)
+        assert np.array_equal(fused.get_populations(), single.get_populations())
+
+
+def test_save_state_between_groups():
+    """The raw state after a fused call is that of single steps (solid slots included)."""
+    import torch
+    announce("fused steps, raw state")
+    fused, _ = _lattice(150, 50, "f64", "solid", 3)
+    single, _ = _lattice(150, 50, "f64", "solid", 3)
+    fused.step(13)
+    for _ in range(13):
+        single.step(1)
+    n = fused.state_bytes()
+    a = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    b = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    fused.save_state(a)
+    single.save_state(b)
+    assert torch.equal(a, b)
