@@ -1492,24 +1492,43 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
 int max_fused_steps(const DevState &s)
 {
     // the full-way rule reads the state of two steps back from the other lattice
-    if (s.layout != kDenseAB || s.fullway)
+    if (s.fullway || !s.f[1])
+        return 1;
+    if (s.fluid_frac == 0.0)
+        return 1;
+    // The fused kernel's time goes with the mesh area, a single sparse step's with the
+    // fluid nodes, and the lines are where they meet.  Measured, 4096^2 discs with a
+    // force, us per step, fused against single: INDIRECT FP64 131 / 217 at fluid
+    // fraction 0.5, 118 / 89 at 0.2; FP32 97 / 113, 96 / 46; 16 bits 104 / 90 at 0.5,
+    // 104 / 140 at 0.9.  TILED16 FP64 146 / 237, 128 / 106; FP32 107 / 123, 98 / 56;
+    // 16 bits 115 / 93 at 0.5, 114 / 145 at 0.9.
+    if (s.layout == kIndirect && s.fluid_frac < (s.dtype == kF64 ? 0.32 : s.dtype == kF32 ? 0.45 : 0.65))
+        return 1;
+    if (s.layout == kTiled16 && s.fluid_frac < (s.dtype == kF64 ? 0.34 : s.dtype == kF32 ? 0.45 : 0.75))
         return 1;
     // StepsShape::kMax
     const bool force = s.gx != 0.0 || s.gy != 0.0;
-    return s.mrt || s.open || s.alpha || (s.trt && force) ? 6 : 8;
+    const bool sparse = s.layout == kTiled16 || s.layout == kIndirect;
+    return s.mrt || s.open || s.alpha || (s.trt && force) ||
+                   (sparse && s.dtype != kF64 && (s.trt || force))
+               ? 6
+               : 8;
 }
 
 hipError_t launch_steps(const DevState &s, int cur, int steps)
 {
-    if (steps < 2 || steps > max_fused_steps(s))
+    if (steps < 2 || steps > max_fused_steps(s) || (s.layout == kDenseAA && steps % 2 != 0))
         return hipErrorInvalidValue;
-    switch (s.dtype) {
-    case kF64: return launch_steps_f64(s, cur, steps);
-    case kF32: return launch_steps_f32(s, cur, steps);
-    case kF16S: return launch_steps_f16(s, cur, steps);
-    case kBF16S: return launch_steps_bf16(s, cur, steps);
-    }
-    return hipErrorInvalidValue;
+    typedef hipError_t (*launch)(const DevState &, int, int);
+    static const launch table[4][4] = {
+        {launch_steps_dense_f64, launch_steps_dense_f32, launch_steps_dense_f16,
+         launch_steps_dense_bf16},
+        {launch_steps_aa_f64, launch_steps_aa_f32, launch_steps_aa_f16, launch_steps_aa_bf16},
+        {launch_steps_tiles_f64, launch_steps_tiles_f32, launch_steps_tiles_f16,
+         launch_steps_tiles_bf16},
+        {launch_steps_list_f64, launch_steps_list_f32, launch_steps_list_f16,
+         launch_steps_list_bf16}};
+    return table[s.layout][s.dtype](s, cur, steps);
 }
 
 hipError_t launch_scatter_canonical(const DevState &s, int64_t t, int cur, const double *fc,

@@ -31,7 +31,8 @@ struct DevState {
     int nx = 0, ny = 0;
     int pitch = 0;        // dense: row pitch in elements (multiple of 64)
     size_t plane = 0;     // elements per population plane of one lattice
-    void *f[2] = {nullptr, nullptr};  // lattices (f[1] unused by DENSE_AA)
+    void *f[2] = {nullptr, nullptr};  // lattices (DENSE_AA: f[1] = second lattice of
+                                      // launch_steps, null if there is none)
     const uint8_t *type = nullptr;    // node-type codes (dense / tiled)
     const uint8_t *nmask = nullptr;   // solid-neighbour bits (dense / tiled)
     const uint32_t *seg_interior = nullptr;  // dense: per 256-node row segment, 1 = all interior
@@ -44,6 +45,13 @@ struct DevState {
     const uint32_t *ind_pk = nullptr;                       // INDIRECT: packed row offsets
     const uint16_t *ind_info = nullptr;                     // INDIRECT: solid bits + edge flag
     const int32_t *ind_edge = nullptr;                      // INDIRECT: edge-node table [][8]
+    double fluid_frac = 0.0;  // fluid nodes over mesh nodes
+    // sparse layouts: fluid bits of the 64-column chunks [ny][pitch / 64]; INDIRECT:
+    // list index of each chunk's first fluid node; TILED16: tile index of every
+    // 16 x 16 square [ny / 16][nx / 16], -1 where none is kept
+    const uint64_t *chunk_fluid = nullptr;
+    const uint32_t *chunk_first = nullptr;
+    const int32_t *tile_of = nullptr;
     const double *bc_val = nullptr;   // open-boundary values [node][2], same indexing as
                                       // alpha; read only at open-boundary nodes
     int open = 0;                     // 1 when the node types hold open-boundary codes
@@ -73,12 +81,19 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur);
 // Most steps one launch_steps call takes (1: this lattice runs single steps only).
 int max_fused_steps(const DevState &s);
 // `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in
-// one launch (DENSE_AB), bitwise those of `steps` launch_step calls.
+// one launch, bitwise those of `steps` launch_step calls.  DENSE_AA: from f[0] to
+// f[1], an even number of steps from an odd time step.
 hipError_t launch_steps(const DevState &s, int cur, int steps);
-hipError_t launch_steps_f64(const DevState &s, int cur, int steps);
-hipError_t launch_steps_f32(const DevState &s, int cur, int steps);
-hipError_t launch_steps_f16(const DevState &s, int cur, int steps);
-hipError_t launch_steps_bf16(const DevState &s, int cur, int steps);
+#define LBM_DECLARE_STEPS(place)                                              \
+    hipError_t launch_steps_##place##_f64(const DevState &, int, int);        \
+    hipError_t launch_steps_##place##_f32(const DevState &, int, int);        \
+    hipError_t launch_steps_##place##_f16(const DevState &, int, int);        \
+    hipError_t launch_steps_##place##_bf16(const DevState &, int, int);
+LBM_DECLARE_STEPS(dense)
+LBM_DECLARE_STEPS(aa)
+LBM_DECLARE_STEPS(list)
+LBM_DECLARE_STEPS(tiles)
+#undef LBM_DECLARE_STEPS
 
 // Canonical populations fc (device FP64 [9][ny][pitch]) -> stored state at step t.
 // Full-way rule: fc's wall slots become the populations in flight; with

@@ -19,12 +19,13 @@
 // steps.  Boundary nodes: the node types travel with the rows; a row of interior
 // nodes (one ballot) skips the bounce-back selects.
 //
-// Measured, Taylor-Green 4096^2, us per step (single steps before): FP64 400 -> 117
-// (8 steps a launch), FP32 192 -> 61, FP16 103 -> 65.  The FP32 and 16-bit kernels are
-// then bound by VALU issue (95 % of it at FP32), FP64 by VALU (0.6) and memory
-// together.  A form that kept all K steps in one wavefront (rows in registers, lane
-// shifts instead of LDS) ran FP64 125, FP32 68, FP16 75 at its best K = 4, 4, 2: K is
-// bounded by the registers there, and boundary handling spilled them.
+// Measured, Taylor-Green 4096^2, us per step (K single launches before): FP64
+// 400 -> 105 (8 steps), FP32 192 -> 50, FP16 103 -> 47; with node types 110, 54,
+// 51.  The FP32 and 16-bit kernels are then bound by VALU issue (95 % of it at
+// FP32), FP64 by both memory (0.65 of its rate) and VALU.  A form that kept all K
+// steps in one wavefront (rows in registers, lane shifts instead of LDS) ran
+// FP64 125, FP32 68, FP16 75 at its best K = 4, 4, 2: K is bounded by the
+// registers there, and boundary handling spilled them.
 #pragma once
 
 #include <algorithm>
@@ -37,15 +38,47 @@
 namespace lbm {
 namespace {
 
+// Where population i of a node lies.  kDense: the dense A-B lattice.  kDenseOpp:
+// the AA lattice after an odd number of steps, which holds the post-collision
+// f_i in slot opp(i) of its own node, that is the A-B state with the slots of
+// opposite directions exchanged.  kList, kTiles: the sparse layouts.
+enum Place : int { kDense = 0, kDenseOpp = 1, kList = 2, kTiles = 3 };
+
 struct StripGeom {
     uint32_t nstrips;
     int steps;  // K
     int halo;   // columns at each side of a strip that only feed it
     int rows;   // rows a workgroup updates
+    // sparse layouts: fluid bits of the 64-column chunks of every row, and
+    // INDIRECT: the list index of each chunk's first fluid node and the nodes'
+    // info words, TILED16: the tile index of every 16 x 16 square (-1: none)
+    const uint64_t *chunk_fluid;
+    const uint32_t *chunk_first;
+    const uint16_t *info;
+    const int32_t *tile_of;
+    uint32_t n_fluid;
 };
 
 // Slot of direction i among those of equal c_i.y (rows kept in registers).
 __device__ constexpr int kLineOf[9] = {0, 1, 0, 2, 0, 1, 2, 1, 2};
+
+// The stored value b where `m` is all ones, a where it is zero.
+template <class M>
+__device__ __forceinline__ M select_bits(M a, M b, uint32_t m)
+{
+    if constexpr (sizeof(M) == 8) {
+        const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+        const uint32_t lo = ((uint32_t)y & m) | ((uint32_t)x & ~m);
+        const uint32_t hi = ((uint32_t)(y >> 32) & m) | ((uint32_t)(x >> 32) & ~m);
+        return __builtin_bit_cast(M, ((uint64_t)hi << 32) | lo);
+    } else if constexpr (sizeof(M) == 4) {
+        const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+        return __builtin_bit_cast(M, (y & m) | (x & ~m));
+    } else {
+        const uint32_t x = __builtin_bit_cast(uint16_t, a), y = __builtin_bit_cast(uint16_t, b);
+        return __builtin_bit_cast(M, (uint16_t)((y & m) | (x & ~m)));
+    }
+}
 
 // Barrier that orders LDS only: global loads and stores stay in flight.
 __device__ __forceinline__ void lds_barrier()
@@ -57,7 +90,9 @@ __device__ __forceinline__ void lds_barrier()
 
 // LDS layout of a strip: rows between groups, then node types and drag
 // coefficients of the rows in flight (the last step lags 2 K - 1 rows behind the
-// source, and one row is being written).
+// source, and one row is being written), and what the sparse layouts need to place
+// the result: the list index of each wavefront's first kept column, or the tiles of
+// the (at most three) tile rows in flight; with open boundaries every node's index.
 template <class M, int S>
 struct StripLds {
     static constexpr int kWid = 64 * S;
@@ -67,16 +102,19 @@ struct StripLds {
     {
         return (uint32_t)(K * 2 * 9 * kLp) * (uint32_t)sizeof(M);
     }
-    static __host__ __device__ constexpr uint32_t bytes(int K, bool walls, bool drag)
+    static __host__ __device__ constexpr uint32_t bytes(int K, bool walls, bool drag, bool open,
+                                                        int place)
     {
-        return ring_bytes(K) + (uint32_t)(node_rows(K) * kWid) * ((walls ? 2u : 0u) + (drag ? 4u : 0u));
+        const uint32_t rows = (uint32_t)node_rows(K), n = rows * (uint32_t)kWid;
+        return ring_bytes(K) + n * ((walls ? 2u : 0u) + (drag ? 4u : 0u)) +
+               (place < kList ? 0u : open ? 4u * n : place == kList ? 4u * rows * S : 16u * kWid);
     }
 };
 
 // WALLS = false: the lattice has interior fluid nodes only.  MAXK: the most
 // groups a launch may have (block size 64 S K).  LB: wavefronts per SIMD the
 // registers have to allow.
-template <class ST, int PH, bool WALLS, int S, int MAXK, int LB>
+template <class ST, int PH, bool WALLS, int PLACE, int S, int MAXK, int LB>
 __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST> k,
                                                              const StripGeom g)
 {
@@ -85,13 +123,20 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
     using L = StripLds<M, S>;
     constexpr bool DRAG = (PH & 3) == kDragged, FORCE = (PH & 3) != kBGK, TRT = (PH & kTRT) != 0,
                    MRT = (PH & kMRT) != 0, OPEN = (PH & kOpenBC) != 0;
-    static_assert(WALLS || !OPEN, "open boundaries need the node types");
+    constexpr bool SPARSE = PLACE >= kList;
+    static_assert(WALLS || (!OPEN && !SPARSE), "the node types are needed");
+    constexpr uint32_t DS = PLACE == kTiles ? kTileStride : kChunk;  // direction stride
     extern __shared__ __align__(16) unsigned char lds[];
     const int K = g.steps, NR = L::node_rows(K);
     auto ring = reinterpret_cast<M(*)[2][9][L::kLp]>(lds);
     auto node = reinterpret_cast<uint16_t(*)[L::kWid]>(lds + L::ring_bytes(K));
     auto drag = reinterpret_cast<float(*)[L::kWid]>(
         lds + L::ring_bytes(K) + (WALLS ? (uint32_t)(NR * L::kWid) * 2u : 0u));
+    uint32_t *const place_lds = reinterpret_cast<uint32_t *>(
+        lds + L::ring_bytes(K) + (uint32_t)(NR * L::kWid) * (DRAG ? 6u : 2u));
+    auto index = reinterpret_cast<uint32_t(*)[L::kWid]>(place_lds);  // OPEN: [NR]
+    auto first_kept = reinterpret_cast<uint32_t(*)[S]>(place_lds);   // kList: [NR]
+    auto tile_row = reinterpret_cast<int32_t(*)[L::kWid]>(place_lds);  // kTiles: [4]
 
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int j = w / S;                                         // this group's step
@@ -121,23 +166,76 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
         M v[9];
         uint32_t ty, nm;
         float al;
+        uint32_t n;  // sparse: node index (a neighbour's where there is no fluid node)
     } next;
     int ly = wrap_row(y0 - K);
-    auto load_row = [&]() {
-        const M *__restrict__ s = k.src + (uint64_t)(uint32_t)ly * row;
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            next.v[i] = (s + i * (int)kChunk)[co];
-        const uint32_t n = (uint32_t)ly * (uint32_t)k.pitch + (uint32_t)x;
-        if constexpr (WALLS) {
-            next.ty = k.type[n];
-            next.nm = k.nmask[n];
+    // sparse: chunk and tile entries of row ly, loaded one row before its nodes
+    uint64_t fl = 0;
+    uint32_t c_first = 0;
+    int32_t tile = -1;
+    auto load_index = [&]() {
+        if constexpr (SPARSE) {
+            const uint32_t c = (uint32_t)ly * ((uint32_t)k.pitch / kChunk) + ((uint32_t)x >> 6);
+            fl = g.chunk_fluid[c];
+            if constexpr (PLACE == kList)
+                c_first = g.chunk_first[c];
+            else
+                tile = g.tile_of[((uint32_t)ly >> 4) * ((uint32_t)nx >> 4) + ((uint32_t)x >> 4)];
         }
-        if constexpr (DRAG)
-            next.al = k.alpha[n];
-        ly = ly + 1 == ny ? 0 : ly + 1;
+    };
+    auto load_row = [&]() {
+        if constexpr (!SPARSE) {
+            const M *__restrict__ s = k.src + (uint64_t)(uint32_t)ly * row;
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                next.v[i] = (s + (PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS)[co];
+            const uint32_t n = (uint32_t)ly * (uint32_t)k.pitch + (uint32_t)x;
+            if constexpr (WALLS) {
+                next.ty = k.type[n];
+                next.nm = k.nmask[n];
+            }
+            if constexpr (DRAG)
+                next.al = k.alpha[n];
+            ly = ly + 1 == ny ? 0 : ly + 1;
+        } else {
+            const uint32_t bit = (uint32_t)x & 63u;
+            const bool fluid = (fl >> bit) & 1u;
+            uint32_t n, o;
+            if constexpr (PLACE == kList) {
+                // lanes without a fluid node read the next one's populations: no
+                // line more than their neighbours touch, and nothing uses them
+                n = min(c_first + (uint32_t)__popcll(fl & ((uint64_t(1) << bit) - 1u)),
+                        g.n_fluid - 1u);
+                o = list_base(n);
+                const uint32_t inf = g.info[n];
+                next.nm = inf;
+                next.ty = fluid ? 0u : 1u;
+            } else {
+                const uint32_t lx = (uint32_t)x & 15u, l = (uint32_t)ly & 15u;
+                const uint32_t t = tile < 0 ? 0u : (uint32_t)tile;
+                n = t * (uint32_t)kTileNodes + l * 16u + lx;
+                o = tile_base(t, tile_slot(lx, l));
+                next.nm = k.nmask[n];
+                next.ty = OPEN ? (uint32_t)k.type[n] : 0u;
+                next.ty = fluid ? next.ty : (uint32_t)kSolid;
+            }
+            next.n = n;
+            if (fluid || PLACE == kList) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    next.v[i] = k.src[(uint32_t)i * DS + o];
+            }
+            if constexpr (DRAG)
+                next.al = k.alpha[n];
+            ly = ly + 1 == ny ? 0 : ly + 1;
+            load_index();
+        }
     };
     int nput = 0;  // slot of the next row's node data
+    // lane of this wavefront's first kept column
+    const int kept0 = max(0, g.halo - (w - j * S) * 64);
+    const int tile_shift = wrap_row(y0 - K) & 15;  // rows above the source's first in its tile
+    int tput = tile_shift;
     auto put_row = [&](M (&d)[9][L::kLp]) {
 #pragma unroll
         for (int i = 0; i < 9; ++i)
@@ -146,11 +244,27 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
             // two byte stores: were the bytes joined, the compiler would do it
             // (and wait for the row's loads) right after issuing them
             uint8_t *b = reinterpret_cast<uint8_t *>(&node[nput][q]);
-            b[0] = (uint8_t)next.ty;
-            b[1] = (uint8_t)next.nm;
+            if constexpr (PLACE == kList) {
+                // info word: solid neighbours in bits 0-7, boundary code in 9-12
+                const uint32_t code = (next.nm >> 9) & 15u;
+                b[0] = (uint8_t)(next.ty ? (uint32_t)kSolid : code ? code + kOpen - 1u : (uint32_t)kFluid);
+                b[1] = (uint8_t)next.nm;
+            } else {
+                b[0] = (uint8_t)next.ty;
+                b[1] = (uint8_t)next.nm;
+            }
         }
         if constexpr (DRAG)
             drag[nput][q] = next.al;
+        if constexpr (SPARSE && OPEN) {
+            index[nput][q] = next.n;
+        } else if constexpr (PLACE == kList) {
+            if ((int)(threadIdx.x & 63u) == kept0)
+                first_kept[nput][w] = next.n;
+        } else if constexpr (PLACE == kTiles) {
+            tile_row[(tput >> 4) & 3][q] = (int32_t)(next.n / (uint32_t)kTileNodes);
+            ++tput;
+        }
         nput = nput + 1 == NR ? 0 : nput + 1;
     };
 
@@ -162,6 +276,7 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
     for (int i = 0; i < 9; ++i)
         own[i] = M(0);
     if (j == 0) {
+        load_index();
         load_row();
         put_row(ring[0][0]);
         load_row();
@@ -188,17 +303,26 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
         float al = 0.0f;
         if constexpr (DRAG)
             al = drag[slot == 0 ? NR - 1 : slot - 1][q];
+        M v[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            v[i] = kCy[i] > 0 ? up[p][kLineOf[i]] : kCy[i] == 0 ? mid[kLineOf[i]] : n[i];
+        if constexpr (WALLS) {
+            if (__ballot(cd != 0) != 0) {
+                // bit 7 + i of the node data: x - c_i is solid
+#pragma unroll
+                for (int i = 1; i < 9; ++i)
+                    v[i] = select_bits(v[i], own[kOpp[i]],
+                                       (uint32_t)((int32_t)(cd << (24 - i)) >> 31));
+            }
+        }
         R f[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            f[i] = ST::ld(kCy[i] > 0 ? up[p][kLineOf[i]] : kCy[i] == 0 ? mid[kLineOf[i]] : n[i], i);
+            f[i] = ST::ld(v[i], i);
         if constexpr (WALLS) {
-            if (__ballot(cd != 0) != 0) {
-                const uint32_t sm = cd >> 8;
-#pragma unroll
-                for (int i = 1; i < 9; ++i)
-                    f[i] = (sm >> (i - 1)) & 1u ? ST::ld(own[kOpp[i]], i) : f[i];
-                if constexpr (OPEN) {
+            if constexpr (OPEN) {
+                if (__ballot(cd != 0) != 0) {
                     if (const unsigned o = open_code((uint8_t)cd)) {
                         R a0, a1;
                         open_values<R, ST::kShift>(o, bv0, bv1, a0, a1);
@@ -214,8 +338,9 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
                     own[i] = kCx[i] == 0 ? n[i] : r[i][q + 1];
                 if constexpr (OPEN) {
                     if (open_code((uint8_t)node_c)) {
-                        const double *v = k.bc_val +
-                                          2 * ((size_t)(uint32_t)yn * k.pitch + (uint32_t)x);
+                        const size_t n = SPARSE ? (size_t)index[slot][q]
+                                                : (size_t)(uint32_t)yn * k.pitch + (uint32_t)x;
+                        const double *v = k.bc_val + 2 * n;
                         bv0 = v[0];
                         bv1 = v[1];
                     }
@@ -231,18 +356,54 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
         }
         if (!whole)
             return;
+        if constexpr (SPARSE) {
+            if (__ballot((cd & 0xFFu) != kSolid) == 0)
+                return;  // solid nodes only: nothing uses what they would get
+        }
         collide<R, DRAG, ST::kShift, FORCE, ST::kExact, TRT, MRT>(f, k.omega, k.gx, k.gy,
                                                                  DRAG ? (R)al : R(0), k.rt);
+        uint64_t kept_fluid = 0;
+        if constexpr (PLACE == kList && !OPEN)
+            kept_fluid = __ballot(keep && (cd & 0xFFu) != kSolid);
         if (j < K - 1) {
             M(&d)[9][L::kLp] = ring[j + 1][p ^ 1];
 #pragma unroll
             for (int i = 0; i < 9; ++i)
                 d[i][q + 1] = ST::st(f[i], i);
         } else if (keep && (cd & 0xFFu) != kSolid) {
-            M *__restrict__ d = k.dst + (uint64_t)(uint32_t)yo * row;
+            if constexpr (!SPARSE) {
+                M *__restrict__ d = k.dst + (uint64_t)(uint32_t)yo * row;
 #pragma unroll
-            for (int i = 0; i < 9; ++i)
-                store_nt(&(d + i * (int)kChunk)[co], ST::st(f[i], i));
+                for (int i = 0; i < 9; ++i)
+                    store_nt(&(d + (PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS)[co],
+                             ST::st(f[i], i));
+            } else {
+                uint32_t o;
+                if constexpr (PLACE == kList) {
+                    const int sc = slot == 0 ? NR - 1 : slot - 1;
+                    if constexpr (OPEN)
+                        o = list_base(index[sc][q]);
+                    else  // kept columns never cross the seam: count the fluid ones before
+                        o = list_base(first_kept[sc][w - j * S] +
+                                      __builtin_amdgcn_mbcnt_hi(
+                                          (uint32_t)(kept_fluid >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((uint32_t)kept_fluid, 0u)));
+                } else {
+                    uint32_t t;
+                    if constexpr (OPEN)
+                        t = index[slot == 0 ? NR - 1 : slot - 1][q] / (uint32_t)kTileNodes;
+                    else
+                        t = (uint32_t)tile_row[((yo - y0 + K + tile_shift) >> 4) & 3][q];
+                    o = tile_base(t, tile_slot((uint32_t)x & 15u, (uint32_t)yo & 15u));
+                }
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    if constexpr (PLACE == kTiles)
+                        k.dst[(uint32_t)i * DS + o] = ST::st(f[i], i);
+                    else
+                        store_nt(&k.dst[(uint32_t)i * DS + o], ST::st(f[i], i));
+                }
+            }
         }
     };
     const int T = rows + 3 * K - 1;
@@ -276,11 +437,12 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
 // step against 65 at 4096^2, FP64 with drag 169 against 130).  Six FP64 steps use
 // S = 2, since a workgroup whose wavefronts are no multiple of four loads the
 // SIMDs unevenly (FP64, six steps, S = 1: 190 us per step against 118).
-template <class ST, int PH>
+template <class ST, int PH, int PLACE>
 struct StepsShape {
     static constexpr bool kHeavy = (PH & (kMRT | kOpenBC)) != 0 || (PH & 3) == kDragged ||
                                    ((PH & kTRT) != 0 && (PH & 3) != kBGK);
-    static constexpr bool kFull = (PH & kMRT) != 0 && (PH & kOpenBC) != 0 && (PH & 3) != kBGK;
+    static constexpr bool kFull = (PH & kMRT) != 0 && (PH & 3) != kBGK &&
+                                  ((PH & kOpenBC) != 0 || PLACE >= kList);
     static constexpr bool kF64 = sizeof(typename ST::mem) == 8;
     static constexpr int S = kF64 && !kHeavy ? 1 : 2;
     static constexpr int kMax = kHeavy ? 6 : 8;
@@ -317,12 +479,12 @@ inline int strip_rows(int ny, uint32_t nstrips, int K, int per_cu)
     return best_rows;
 }
 
-template <class ST, int PH, bool WALLS>
+template <class ST, int PH, bool WALLS, int PLACE>
 void steps_launch(const DevState &s, int cur, int K)
 {
     using M = typename ST::mem;
     using R = typename ST::real;
-    using Sh = StepsShape<ST, PH>;
+    using Sh = StepsShape<ST, PH, PLACE>;
     constexpr int S = Sh::S;
     using L = StripLds<M, S>;
     const uint32_t bpr = (uint32_t)((s.nx + 255) / 256);
@@ -348,45 +510,55 @@ void steps_launch(const DevState &s, int cur, int K)
     g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
     const int out = L::kWid - 2 * g.halo;
     g.nstrips = (uint32_t)((s.nx + out - 1) / out);
-    const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged);
+    const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged, (PH & kOpenBC) != 0,
+                                  PLACE);
+    g.chunk_fluid = s.chunk_fluid;
+    g.chunk_first = s.chunk_first;
+    g.info = s.ind_info;
+    g.tile_of = s.tile_of;
+    g.n_fluid = (uint32_t)s.n_fluid;
     const int per_cu = std::max(1, std::min((int)(163840u / lds), Sh::kWaves * 4 / (S * K)));
     g.rows = strip_rows(s.ny, g.nstrips, K, per_cu);
     const uint32_t blocks = g.nstrips * (uint32_t)((s.ny + g.rows - 1) / g.rows);
-    k_steps<ST, PH, WALLS, S, Sh::kMax, Sh::kWaves>
+    k_steps<ST, PH, WALLS, PLACE, S, Sh::kMax, Sh::kWaves>
         <<<blocks, (uint32_t)(64 * S * K), lds, s.stream>>>(k, g);
 }
 
-template <class ST, int COLL>
+template <class ST, int COLL, int PLACE>
 void steps_phys(const DevState &s, int cur, int K)
 {
     const bool force = s.gx != 0.0 || s.gy != 0.0;
     if (s.open) {
         if (s.alpha)
-            steps_launch<ST, kDragged | kOpenBC | COLL, true>(s, cur, K);
+            steps_launch<ST, kDragged | kOpenBC | COLL, true, PLACE>(s, cur, K);
         else if (force)
-            steps_launch<ST, kForced | kOpenBC | COLL, true>(s, cur, K);
+            steps_launch<ST, kForced | kOpenBC | COLL, true, PLACE>(s, cur, K);
         else
-            steps_launch<ST, kBGK | kOpenBC | COLL, true>(s, cur, K);
+            steps_launch<ST, kBGK | kOpenBC | COLL, true, PLACE>(s, cur, K);
     } else if (s.alpha) {
-        steps_launch<ST, kDragged | COLL, true>(s, cur, K);
+        steps_launch<ST, kDragged | COLL, true, PLACE>(s, cur, K);
     } else if (force) {
-        steps_launch<ST, kForced | COLL, true>(s, cur, K);
-    } else if (s.interior_frac == 1.0) {
-        steps_launch<ST, kBGK | COLL, false>(s, cur, K);
+        steps_launch<ST, kForced | COLL, true, PLACE>(s, cur, K);
     } else {
-        steps_launch<ST, kBGK | COLL, true>(s, cur, K);
+        if constexpr (PLACE < kList) {
+            if (s.interior_frac == 1.0) {
+                steps_launch<ST, kBGK | COLL, false, PLACE>(s, cur, K);
+                return;
+            }
+        }
+        steps_launch<ST, kBGK | COLL, true, PLACE>(s, cur, K);
     }
 }
 
-template <class ST>
-hipError_t steps_typed(const DevState &s, int cur, int K)
+template <class ST, int PLACE>
+hipError_t steps_placed(const DevState &s, int cur, int K)
 {
     if (s.mrt)
-        steps_phys<ST, kMRT>(s, cur, K);
+        steps_phys<ST, kMRT, PLACE>(s, cur, K);
     else if (s.trt)
-        steps_phys<ST, kTRT>(s, cur, K);
+        steps_phys<ST, kTRT, PLACE>(s, cur, K);
     else
-        steps_phys<ST, 0>(s, cur, K);
+        steps_phys<ST, 0, PLACE>(s, cur, K);
     return hipGetLastError();
 }
 

@@ -67,6 +67,25 @@ double interior_fraction(const std::vector<uint32_t> &flags)
     return (double)n / (double)flags.size();
 }
 
+void chunk_fluid(const uint8_t *mask, int nx, int ny, int cpr, std::vector<uint64_t> &bits,
+                 std::vector<uint32_t> &first)
+{
+    bits.assign((size_t)ny * cpr, 0);
+    first.assign((size_t)ny * cpr, 0);
+    uint32_t before = 0;
+    for (int y = 0; y < ny; ++y)
+        for (int c = 0; c < cpr; ++c) {
+            const uint8_t *m = mask + (size_t)y * nx + 64 * c;
+            const int w = std::min(64, nx - 64 * c);
+            uint64_t b = 0;
+            for (int l = 0; l < w; ++l)
+                b |= (uint64_t)(m[l] == 0) << l;
+            bits[(size_t)y * cpr + c] = b;
+            first[(size_t)y * cpr + c] = before;
+            before += (uint32_t)__builtin_popcountll(b);
+        }
+}
+
 Tiles tiles16(const uint8_t *mask, int nx, int ny, bool keep_all)
 {
     Tiles t;

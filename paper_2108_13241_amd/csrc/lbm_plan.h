@@ -40,6 +40,12 @@ struct Tiles {
 };
 // nx, ny must be multiples of 16.  keep_all: keep empty (all-solid) tiles too.
 Tiles tiles16(const uint8_t *mask, int nx, int ny, bool keep_all = false);
+// Fluid bits of the 64-column chunks of every row, [ny][cpr] words: bit l of word
+// y * cpr + c set <=> node (64 c + l, y) is fluid.  first[y * cpr + c]: the number of
+// fluid nodes before that chunk in row-major order (its first fluid node's index in
+// Fluid).
+void chunk_fluid(const uint8_t *mask, int nx, int ny, int cpr, std::vector<uint64_t> &bits,
+                 std::vector<uint32_t> &first);
 // Tile-layout type codes / nmask / node lists ([n_tiles][256]).
 void tiled_types(const uint8_t *mask, int nx, int ny, const Tiles &t, std::vector<uint8_t> &type,
                  std::vector<uint8_t> &nmask);

@@ -78,6 +78,7 @@ struct lbm_ctx {
     hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
     int32_t graph_len = 0;
     hipStream_t capture_stream = nullptr;
+    bool no_pair = false;  // AA: the second lattice could not be allocated
     // Overlapped checkpointed adjoint: a second segment buffer (library-owned),
     // an auxiliary stream for the segment recomputation and its events.
     void *seg2 = nullptr;
@@ -415,6 +416,24 @@ int lbm_create(lbm_ctx **out, int32_t nx, int32_t ny, const uint8_t *node_type, 
             return fail_create(rc, "cannot upload the edge-node table");
         s.ind_edge = (const int32_t *)p;
     }
+    s.fluid_frac = (double)c->n_fluid / (double)nn;
+    if (layout == LBM_TILED16 || layout == LBM_INDIRECT) {
+        std::vector<uint64_t> bits;
+        std::vector<uint32_t> first;
+        lbm::plan::chunk_fluid(node_type, nx, ny, (int)(pitch / 64), bits, first);
+        if ((rc = upload(bits.data(), bits.size() * 8, &p)))
+            return fail_create(rc, "cannot upload the fluid bits");
+        s.chunk_fluid = (const uint64_t *)p;
+        if (layout == LBM_INDIRECT) {
+            if ((rc = upload(first.data(), first.size() * 4, &p)))
+                return fail_create(rc, "cannot upload the chunk offsets");
+            s.chunk_first = (const uint32_t *)p;
+        } else {
+            if ((rc = upload(c->tiles.index_of.data(), c->tiles.index_of.size() * 4, &p)))
+                return fail_create(rc, "cannot upload the tile index");
+            s.tile_of = (const int32_t *)p;
+        }
+    }
     if (layout != LBM_DENSE_AB && layout != LBM_DENSE_AA &&
         (uint64_t)9 * s.plane >= (uint64_t(1) << 32))
         return fail_create(LBM_ERR_UNSUPPORTED, "lattice too large for 32-bit offsets");
@@ -702,18 +721,38 @@ int lbm_set_force(lbm_ctx *c, const double *force)
     return LBM_OK;
 }
 
+// Largest second lattice the AA layout allocates for its fused steps; larger
+// lattices are stepped in place.
+constexpr size_t kPairBudget = size_t(2) << 30;
+
+// Most steps a launch may take on this context.
+static int fused_limit(const lbm_ctx *c)
+{
+    lbm::DevState s = c->s;
+    if (s.layout == LBM_DENSE_AA && !s.f[1]) {
+        // the second lattice is allocated on the first call that uses it
+        if (c->no_pair || (size_t)9 * s.plane * c->pop_bytes > kPairBudget)
+            return 1;
+        s.f[1] = s.f[0];
+    }
+    return lbm::max_fused_steps(s);
+}
+
 // Graph length for this context: explicit setting, or (auto) 32 steps for
-// lattices small enough that host launch overhead is a visible share of a step.
+// lattices small enough that host launch overhead is a visible share of a step
+// and that run one launch per step.
 static int32_t graph_length(const lbm_ctx *c)
 {
     if (c->graph_steps >= 0)
         return c->graph_steps;
+    if (fused_limit(c) > 1)
+        return 0;
     const double bytes = 18.0 * (double)c->s.plane * c->pop_bytes;
     return bytes < 128.0 * (1 << 20) ? 32 : 0;
 }
 
-// Launch the next `steps` steps (one kernel; steps > 1 only where the layout has
-// the fused kernel) and advance the counters.
+// Launch the next `steps` steps (one kernel; steps > 1 only where fused_limit
+// allows it) and advance the counters.
 static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
 {
     lbm::DevState s = c->s;
@@ -721,25 +760,74 @@ static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
     hipError_t e = steps > 1 ? lbm::launch_steps(s, c->cur, steps) : lbm::launch_step(s, c->t, c->cur);
     if (c->s.layout != LBM_DENSE_AA)
         c->cur ^= 1;
+    else if (steps > 1)
+        std::swap(c->s.f[0], c->s.f[1]);
     c->t += steps;
     return e;
 }
 
-// Launch n steps in as few launches as the fused kernel allows (an even number
-// of launches if `even`: the state then returns to the lattice it started from),
-// of equal length as nearly as possible.
-static hipError_t step_groups(lbm_ctx *c, hipStream_t stream, int64_t n, bool even)
+// Launch n steps of a two-lattice layout: the most a launch takes, as often as they
+// fit, then the rest (a launch of fewer steps costs about what its share of the
+// wavefronts does, so equal parts would gain nothing).  keep_parity: as many
+// launches as n, modulo 2, so that a recorded sequence leaves the state in the
+// lattice that n single steps would.
+static hipError_t step_groups(lbm_ctx *c, hipStream_t stream, int64_t n, bool keep_parity)
 {
     const int64_t kmax = lbm::max_fused_steps(c->s);
-    int64_t left = (n + kmax - 1) / kmax;
-    if (even && (left & 1) && left < n)
-        ++left;
     hipError_t e = hipSuccess;
-    for (; left > 0 && e == hipSuccess; --left) {
-        const int64_t steps = (n + left - 1) / left;
+    if (keep_parity && ((((n + kmax - 1) / kmax) ^ n) & 1)) {
+        e = step_group(c, stream, 1);
+        --n;
+        // n steps now, again with launches of n's parity: one more single step
+        // wherever the count would be off
+        if ((((n + kmax - 1) / kmax) ^ n) & 1) {
+            e = e == hipSuccess ? step_group(c, stream, 1) : e;
+            --n;
+        }
+    }
+    while (n > 0 && e == hipSuccess) {
+        const int64_t steps = std::min(n, kmax);
         e = step_group(c, stream, (int)steps);
         n -= steps;
     }
+    return e;
+}
+
+// Launch n steps of the AA layout.  After an odd number of steps its lattice is
+// an A-B lattice with opposite slots exchanged, which the fused kernel advances
+// by an even number of steps into the second lattice; a single in-place step
+// before it (from an even time step) and one after it (to an even one) do the
+// rest.
+static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, bool in_place)
+{
+    hipError_t e = hipSuccess;
+    const int64_t before = (c->t & 1) ? 0 : 1;
+    if (!in_place && n - before >= 2 && fused_limit(c) > 1) {
+        if (!c->s.f[1]) {
+            const size_t b = (size_t)9 * c->s.plane * c->pop_bytes;
+            c->s.f[1] = own_alloc(c, b);
+            c->no_pair = c->s.f[1] == nullptr;
+            if (c->s.f[1]) {
+                lbm::DevState s = c->s;
+                s.stream = stream;
+                e = lbm::launch_rest(s, c->s.f[1]);  // slots no step writes (solid nodes)
+            }
+        }
+        if (c->s.f[1]) {
+            if (before && e == hipSuccess) {
+                e = step_group(c, stream, 1);
+                --n;
+            }
+            const int64_t kmax = lbm::max_fused_steps(c->s);
+            while (n >= 2 && e == hipSuccess) {
+                const int64_t steps = std::min(n & ~int64_t(1), kmax);
+                e = step_group(c, stream, (int)steps);
+                n -= steps;
+            }
+        }
+    }
+    for (; n > 0 && e == hipSuccess; --n)
+        e = step_group(c, stream, 1);
     return e;
 }
 
@@ -755,7 +843,8 @@ static int capture_graph(lbm_ctx *c, int key, int32_t G)
     LBM_HIP(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
     // G is even and so is the number of launches: a replay returns to the parity
     // it started from
-    hipError_t e = step_groups(c, c->capture_stream, G, true);
+    hipError_t e = c->s.layout == LBM_DENSE_AA ? step_aa(c, c->capture_stream, G, true)
+                                               : step_groups(c, c->capture_stream, G, true);
     hipError_t e2 = hipStreamEndCapture(c->capture_stream, &graph);
     c->t = t0;
     c->cur = cur0;
@@ -801,7 +890,18 @@ int lbm_step(lbm_ctx *c, int64_t n)
         c->t += G;
         n -= G;
     }
-    LBM_HIP(c, step_groups(c, c->s.stream, n, false));
+    if (n == 0)
+        return LBM_OK;
+    // While the caller captures the stream into a graph of its own, the launches
+    // have to be repeatable: the AA layout steps in place, the others keep the
+    // parity of the lattice that holds the state.
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool capturing = c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+                           st != hipStreamCaptureStatusNone;
+    if (c->s.layout == LBM_DENSE_AA)
+        LBM_HIP(c, step_aa(c, c->s.stream, n, capturing));
+    else
+        LBM_HIP(c, step_groups(c, c->s.stream, n, capturing));
     return LBM_OK;
 }
 

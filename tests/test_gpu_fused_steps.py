@@ -1,4 +1,4 @@
-"""Several steps per launch (dense A-B) give bitwise the state of as many single steps.
+"""Several steps per launch give bitwise the state of as many single steps, in every layout.
 
 A call of one step runs the single-step kernels, which the other tests pin to the oracle; a
 call of n > 1 steps runs the fused kernel.  Sizes sit at the edges of its strips (48, 56, 112
@@ -16,15 +16,15 @@ SIZES = [(1, 1), (5, 3), (48, 17), (57, 2), (111, 9), (112, 40), (113, 33), (241
 DTYPES = ["f64", "f32", "f16s", "bf16s"]
 
 
-def _lattice(nx, ny, dtype, variant, seed):
+def _lattice(nx, ny, dtype, variant, seed, layout="dense_ab"):
     import paper_2108_13241_amd as lbm
     import synthetic
     kinds = variant.split("+")
     walls = "solid" in kinds
-    m = (synthetic.random_mask(nx, ny, seed=seed, solid_fraction=0.15, walls=ny > 4)
+    m = (synthetic.random_mask(nx, ny, seed=seed, solid_fraction=0.1, walls=ny > 4)
          if walls else synthetic.all_fluid(nx, ny))
     g = (2e-4, -1e-4) if "force" in kinds or "drag" in kinds else (0.0, 0.0)
-    lat = lbm.Lattice(m, 0.7, force=g, dtype=dtype, layout="dense_ab")
+    lat = lbm.Lattice(m, 0.7, force=g, dtype=dtype, layout=layout)
     rng = np.random.default_rng(seed)
     if "drag" in kinds:
         lat.set_porosity(rng.random((ny, nx)).astype(np.float32))
@@ -45,10 +45,10 @@ def _lattice(nx, ny, dtype, variant, seed):
     return lat, m
 
 
-def _check(nx, ny, dtype, variant, counts, seed=11):
-    announce(f"fused steps {nx}x{ny} {dtype} {variant} {counts}")
-    fused, m = _lattice(nx, ny, dtype, variant, seed)
-    single, _ = _lattice(nx, ny, dtype, variant, seed)
+def _check(nx, ny, dtype, variant, counts, seed=11, layout="dense_ab"):
+    announce(f"fused steps {nx}x{ny} {dtype} {layout} {variant} {counts}")
+    fused, m = _lattice(nx, ny, dtype, variant, seed, layout)
+    single, _ = _lattice(nx, ny, dtype, variant, seed, layout)
     for n in counts:
         fused.step(n)
         for _ in range(n):
@@ -75,9 +75,51 @@ def test_variants(variant, dtype):
     _check(131, 37, dtype, variant, [7, 9])
 
 
+@pytest.mark.parametrize("layout", ["dense_ab", "dense_aa", "indirect"])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-def test_step_counts(dtype):
-    _check(150, 50, dtype, "solid", list(range(1, 18)))
+def test_step_counts(dtype, layout):
+    _check(150, 50, dtype, "solid", list(range(1, 18)), layout=layout)
+
+
+@pytest.mark.parametrize("layout", ["dense_aa", "indirect"])
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("nx,ny", SIZES)
+def test_sizes_other_layouts(nx, ny, dtype, layout):
+    _check(nx, ny, dtype, "solid+force", [3, 8, 5], layout=layout)
+
+
+@pytest.mark.parametrize("layout", ["tiled16", "tiled16_all"])
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("nx,ny", [(16, 16), (48, 32), (112, 48), (128, 16), (336, 80)])
+def test_sizes_tiled(nx, ny, dtype, layout):
+    _check(nx, ny, dtype, "solid+force", [3, 8, 5], layout=layout)
+
+
+@pytest.mark.parametrize("layout", ["dense_aa", "indirect", "tiled16"])
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16s"])
+@pytest.mark.parametrize("variant", ["", "trt", "mrt", "force", "solid", "solid+trt+force",
+                                     "solid+drag", "solid+drag+mrt", "open", "open+solid+trt",
+                                     "open+solid+drag+mrt"])
+def test_variants_other_layouts(variant, dtype, layout):
+    _check(144, 48, dtype, variant, [7, 10], layout=layout)
+
+
+@pytest.mark.parametrize("layout", ["indirect", "tiled16"])
+def test_sparse_holes(layout):
+    """Whole solid squares, rows and strips between the fluid nodes, and one fluid node."""
+    import paper_2108_13241_amd as lbm
+    announce(f"fused steps, sparse holes, {layout}")
+    m = np.ones((96, 320), dtype=np.uint8)
+    m[20:45, 30:90] = 0
+    m[60:75, 150:320] = 0
+    m[50, 200] = 0
+    m[0:3, :40] = 0
+    lats = [lbm.Lattice(m, 0.8, force=(1e-4, 2e-4), dtype="f64", layout=layout) for _ in range(2)]
+    lats[0].step(23)
+    for _ in range(23):
+        lats[1].step(1)
+    a, b = (lat.get_populations() for lat in lats)
+    assert np.array_equal(a, b)
 
 
 @pytest.mark.parametrize("graph", [0, 2, 10, 34])
