@@ -1496,9 +1496,12 @@ int max_fused_steps(const DevState &s)
         return 1;
     if (s.fluid_frac == 0.0)
         return 1;
+    int square = 0;
+    if (const int k = square_steps(s.nx, s.ny, s.dtype, square))
+        return k;
     // The fused kernel's time goes with the mesh area, a single sparse step's with the
     // fluid nodes, and the lines are where they meet.  Measured, 4096^2 discs with a
-    // force, us per step, fused against single: INDIRECT FP64 131 / 217 at fluid
+    // force, us per step, fused against single: INDIRECT FP64 122 / 217 at fluid
     // fraction 0.5, 118 / 89 at 0.2; FP32 97 / 113, 96 / 46; 16 bits 104 / 90 at 0.5,
     // 104 / 140 at 0.9.  TILED16 FP64 146 / 237, 128 / 106; FP32 107 / 123, 98 / 56;
     // 16 bits 115 / 93 at 0.5, 114 / 145 at 0.9.
@@ -1510,7 +1513,7 @@ int max_fused_steps(const DevState &s)
     const bool force = s.gx != 0.0 || s.gy != 0.0;
     const bool sparse = s.layout == kTiled16 || s.layout == kIndirect;
     return s.mrt || s.open || s.alpha || (s.trt && force) ||
-                   (sparse && s.dtype != kF64 && (s.trt || force))
+                   (sparse && (s.dtype == kF64 || s.trt || force))
                ? 6
                : 8;
 }

@@ -78,6 +78,35 @@ int64_t reduction_capacity(const DevState &s);
 // even or odd kernel).
 hipError_t launch_step(const DevState &s, int64_t t, int cur);
 
+// Small lattices run the fused steps on squares of n x n nodes: n = 16 or 32 and the
+// most steps a launch then takes (returned); n = 0 for larger lattices (strips).
+// 16 x 16 nodes at four steps while that leaves at most one workgroup per CU; else
+// 32 x 32 at the most steps that do; else four steps, in FP64 up to two rounds of the
+// chip (one workgroup per CU: its LDS), in the narrower types up to three (two per CU).
+// Measured, us per step, FP64: 256 x 64 1.18 (16, 4 steps), 1.36 (32, 8 steps), strips
+// 2.15; 257^2 with a lid 1.64 (32, 6 steps), 2.06 (16, 3 steps), strips 2.75; 512^2
+// 3.9 (32, 4 steps), strips 4.0; FP32 128^2 0.99 (16, 4 steps), 1.02 (32, 8 steps); 400 x
+// 300 1.63 (32, 4 steps), 2.10 (16, 3 steps); 1024 x 256 with drag 2.98 (32, 4 steps), 3.4
+// (32, 6 steps), strips 4.0; with a force FP64 560^2 5.6, strips 4.9; FP32 760^2 5.0,
+// strips 5.7, 900^2 6.9, strips 7.5.
+inline int square_steps(int nx, int ny, int dtype, int &n)
+{
+    auto blocks = [&](int out) {
+        return (int64_t)((nx + out - 1) / out) * ((ny + out - 1) / out);
+    };
+    n = 16;
+    if (blocks(16 - 2 * 4) <= 256)
+        return 4;
+    n = 32;
+    for (int k = 8; k > 4; --k)
+        if (blocks(32 - 2 * k) <= 256)
+            return k;
+    if (blocks(32 - 2 * 4) <= (dtype == kF64 ? 512 : 1500))
+        return 4;
+    n = 0;
+    return 0;
+}
+
 // Most steps one launch_steps call takes (1: this lattice runs single steps only).
 int max_fused_steps(const DevState &s);
 // `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in

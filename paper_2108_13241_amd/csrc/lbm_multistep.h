@@ -428,6 +428,112 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
     }
 }
 
+// ------------------------------------------------------------- small lattices --
+// K steps of a small lattice: a workgroup owns an N x N square of nodes, one per
+// lane, loads what the square stores, and exchanges the populations through LDS
+// once per step (two copies, one barrier).  The square loses one ring of nodes per
+// step and writes the (N - 2 K)^2 inner ones.  Strips need a wavefront row per step
+// and iterate over the rows, so a lattice of some tens of thousands of nodes leaves
+// them waiting on one row after the other; here every node of a step runs at once,
+// and a launch takes little more than its one read of memory and K exchanges.
+// Bounce-back values are the lane's own, still in registers.
+template <class M, int N>
+struct SquareLds {
+    static constexpr int kPad = N + 1;  // the rows and columns beyond the square
+    static constexpr int kPlane = N * N + 2 * kPad;
+};
+
+template <class ST, int PH, int PLACE, int N>
+__global__ __launch_bounds__(N *N) void k_steps_square(const DenseArgs<ST> k, const StripGeom g)
+{
+    using R = typename ST::real;
+    using M = typename ST::mem;
+    using L = SquareLds<M, N>;
+    constexpr bool DRAG = (PH & 3) == kDragged, FORCE = (PH & 3) != kBGK, TRT = (PH & kTRT) != 0,
+                   MRT = (PH & kMRT) != 0, OPEN = (PH & kOpenBC) != 0;
+    constexpr uint32_t DS = PLACE == kTiles ? kTileStride : kChunk;
+    __shared__ M ring[2][9][L::kPlane];
+    const int K = g.steps, out = N - 2 * K;
+    const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int by = (int)(b / g.nstrips), bx = (int)(b - (uint32_t)by * g.nstrips);
+    const int tx = (int)threadIdx.x % N, ty = (int)threadIdx.x / N;
+    const int xu = bx * out - K + tx, yu = by * out - K + ty;  // before the periodic wrap
+    int x = xu % k.nx, y = yu % k.ny;
+    x = x < 0 ? x + k.nx : x;
+    y = y < 0 ? y + k.ny : y;
+    const bool keep = tx >= K && tx < N - K && ty >= K && ty < N - K && xu < k.nx && yu < k.ny;
+    const uint32_t cpr = (uint32_t)k.pitch / kChunk;
+    // the node's place, its index in the per-node arrays, and its types
+    uint64_t o;
+    uint32_t n, type, nm;
+    if constexpr (PLACE == kList) {
+        const uint32_t c = (uint32_t)y * cpr + ((uint32_t)x >> 6), bit = (uint32_t)x & 63u;
+        const uint64_t fl = g.chunk_fluid[c];
+        n = min(g.chunk_first[c] + (uint32_t)__popcll(fl & ((uint64_t(1) << bit) - 1u)),
+                g.n_fluid - 1u);
+        const uint32_t inf = g.info[n], code = (inf >> 9) & 15u;
+        type = (fl >> bit) & 1u ? (code ? code + kOpen - 1u : (uint32_t)kFluid) : (uint32_t)kSolid;
+        nm = inf & 0xFFu;
+        o = list_base(n);
+    } else if constexpr (PLACE == kTiles) {
+        const int32_t t = g.tile_of[((uint32_t)y >> 4) * ((uint32_t)k.nx >> 4) + ((uint32_t)x >> 4)];
+        const uint32_t lx = (uint32_t)x & 15u, l = (uint32_t)y & 15u, kt = t < 0 ? 0u : (uint32_t)t;
+        n = kt * (uint32_t)kTileNodes + l * 16u + lx;
+        type = t < 0 ? (uint32_t)kSolid : (uint32_t)k.type[n];
+        nm = k.nmask[n];
+        o = tile_base(kt, tile_slot(lx, l));
+    } else {
+        n = (uint32_t)y * (uint32_t)k.pitch + (uint32_t)x;
+        type = k.type[n];
+        nm = k.nmask[n];
+        o = dense_base(x, y, cpr);
+    }
+    M v[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+        v[i] = k.src[(uint64_t)((PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS) + o];
+    R al = R(0), b0 = R(0), b1 = R(0);
+    if constexpr (DRAG)
+        al = (R)k.alpha[n];
+    const unsigned code = open_code((uint8_t)type);
+    if constexpr (OPEN) {
+        if (code)
+            open_values<R, ST::kShift>(code, k.bc_val[2 * (size_t)n], k.bc_val[2 * (size_t)n + 1],
+                                       b0, b1);
+    }
+    const int at = (int)threadIdx.x + L::kPad;
+    for (int t = 0; t < K; ++t) {
+        M(&r)[9][L::kPlane] = ring[t & 1];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            r[i][at] = v[i];
+        lds_barrier();
+        // rows of this wavefront that no later step needs any more (or yet)
+        const int lo = __builtin_amdgcn_readfirstlane(ty), hi = lo + (N >= 64 ? 1 : 64 / N) - 1;
+        if (hi <= t || lo >= N - 1 - t)
+            continue;
+        R f[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const M p = r[i][at - kCx[i] - N * kCy[i]];
+            f[i] = ST::ld(i == 0 ? p : select_bits(p, v[kOpp[i]], (uint32_t)((int32_t)(nm << (32 - i)) >> 31)), i);
+        }
+        if constexpr (OPEN) {
+            if (code)
+                apply_open_values<R, ST::kShift>(f, code, b0, b1);
+        }
+        collide<R, DRAG, ST::kShift, FORCE, ST::kExact, TRT, MRT>(f, k.omega, k.gx, k.gy, al, k.rt);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            v[i] = ST::st(f[i], i);
+    }
+    if (keep && type != kSolid) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            k.dst[(uint64_t)((PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS) + o] = v[i];
+    }
+}
+
 // ---------------------------------------------------------------- dispatch --
 
 // Shapes of k_steps.  Eight steps in flight where the registers allow two
@@ -439,8 +545,11 @@ __global__ __launch_bounds__(64 * MAXK * S, LB) void k_steps(const DenseArgs<ST>
 // SIMDs unevenly (FP64, six steps, S = 1: 190 us per step against 118).
 template <class ST, int PH, int PLACE>
 struct StepsShape {
-    static constexpr bool kHeavy = (PH & (kMRT | kOpenBC)) != 0 || (PH & 3) == kDragged ||
-                                   ((PH & kTRT) != 0 && (PH & 3) != kBGK);
+    static constexpr bool kHeavy =
+        (PH & (kMRT | kOpenBC)) != 0 || (PH & 3) == kDragged ||
+        ((PH & kTRT) != 0 && (PH & 3) != kBGK) ||
+        (PLACE >= kList &&
+         (sizeof(typename ST::mem) == 8 || (PH & kTRT) != 0 || (PH & 3) != kBGK));
     static constexpr bool kFull = (PH & kMRT) != 0 && (PH & 3) != kBGK &&
                                   ((PH & kOpenBC) != 0 || PLACE >= kList);
     static constexpr bool kF64 = sizeof(typename ST::mem) == 8;
@@ -506,17 +615,29 @@ void steps_launch(const DevState &s, int cur, int K)
                           Rates<R>{(R)s.omega_m, (R)s.s_e, (R)s.s_eps, (R)s.s_q},
                           0};
     StripGeom g;
-    g.steps = K;
-    g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
-    const int out = L::kWid - 2 * g.halo;
-    g.nstrips = (uint32_t)((s.nx + out - 1) / out);
-    const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged, (PH & kOpenBC) != 0,
-                                  PLACE);
     g.chunk_fluid = s.chunk_fluid;
     g.chunk_first = s.chunk_first;
     g.info = s.ind_info;
     g.tile_of = s.tile_of;
     g.n_fluid = (uint32_t)s.n_fluid;
+    g.steps = K;
+    int square = 0;
+    square_steps(s.nx, s.ny, s.dtype, square);
+    if (square) {
+        const int in = square - 2 * K;
+        g.nstrips = (uint32_t)((s.nx + in - 1) / in);
+        const uint32_t blocks = g.nstrips * (uint32_t)((s.ny + in - 1) / in);
+        if (square == 16)
+            k_steps_square<ST, PH, PLACE, 16><<<blocks, 256, 0, s.stream>>>(k, g);
+        else
+            k_steps_square<ST, PH, PLACE, 32><<<blocks, 1024, 0, s.stream>>>(k, g);
+        return;
+    }
+    g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
+    const int out = L::kWid - 2 * g.halo;
+    g.nstrips = (uint32_t)((s.nx + out - 1) / out);
+    const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged, (PH & kOpenBC) != 0,
+                                  PLACE);
     const int per_cu = std::max(1, std::min((int)(163840u / lds), Sh::kWaves * 4 / (S * K)));
     g.rows = strip_rows(s.ny, g.nstrips, K, per_cu);
     const uint32_t blocks = g.nstrips * (uint32_t)((s.ny + g.rows - 1) / g.rows);

@@ -818,7 +818,7 @@ static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, bool in_pla
                 e = step_group(c, stream, 1);
                 --n;
             }
-            const int64_t kmax = lbm::max_fused_steps(c->s);
+            const int64_t kmax = lbm::max_fused_steps(c->s) & ~1;
             while (n >= 2 && e == hipSuccess) {
                 const int64_t steps = std::min(n & ~int64_t(1), kmax);
                 e = step_group(c, stream, (int)steps);

@@ -3,7 +3,8 @@
 A call of one step runs the single-step kernels, which the other tests pin to the oracle; a
 call of n > 1 steps runs the fused kernel.  Sizes sit at the edges of its strips (48, 56, 112
 and 120 columns), below one strip and one row, and above several strips; step counts cover
-every number of steps per launch and uneven splits.
+every number of steps per launch and uneven splits.  Lattices of up to about 500^2 nodes run
+the fused steps on squares, larger ones on strips.
 """
 import numpy as np
 import pytest
@@ -12,7 +13,8 @@ from gpu_util import announce
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(1, 1), (5, 3), (48, 17), (57, 2), (111, 9), (112, 40), (113, 33), (241, 26), (500, 75)]
+SIZES = [(1, 1), (5, 3), (48, 17), (57, 2), (111, 9), (112, 40), (113, 33), (241, 26), (500, 75),
+         (1, 5000), (7, 9000), (30011, 9), (1009, 601)]
 DTYPES = ["f64", "f32", "f16s", "bf16s"]
 
 
@@ -66,6 +68,15 @@ def test_sizes(nx, ny, dtype):
     _check(nx, ny, dtype, "solid+force", [2, 8, 5])
 
 
+# squares of 16 and 32 nodes at each number of steps, and strips, with a ragged rest
+@pytest.mark.parametrize("layout", ["dense_ab", "dense_aa", "indirect"])
+@pytest.mark.parametrize("dtype", ["f64", "f32", "f16s"])
+@pytest.mark.parametrize("nx,ny", [(129, 121), (250, 241), (285, 283), (321, 309), (351, 347),
+                                   (530, 527), (611, 590)])
+def test_square_sizes(nx, ny, dtype, layout):
+    _check(nx, ny, dtype, "solid+force", [9, 8, 4], layout=layout)
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("variant", ["", "trt", "mrt", "force", "solid", "solid+trt+force",
                                      "solid+mrt+force", "solid+drag", "solid+drag+trt",
@@ -73,6 +84,8 @@ def test_sizes(nx, ny, dtype):
                                      "open+solid+drag+mrt"])
 def test_variants(variant, dtype):
     _check(131, 37, dtype, variant, [7, 9])
+    if dtype in ("f64", "f32"):
+        _check(1031, 577, dtype, variant, [11])
 
 
 @pytest.mark.parametrize("layout", ["dense_ab", "dense_aa", "indirect"])
@@ -90,7 +103,7 @@ def test_sizes_other_layouts(nx, ny, dtype, layout):
 
 @pytest.mark.parametrize("layout", ["tiled16", "tiled16_all"])
 @pytest.mark.parametrize("dtype", DTYPES)
-@pytest.mark.parametrize("nx,ny", [(16, 16), (48, 32), (112, 48), (128, 16), (336, 80)])
+@pytest.mark.parametrize("nx,ny", [(16, 16), (48, 32), (112, 48), (128, 16), (336, 80), (1008, 608)])
 def test_sizes_tiled(nx, ny, dtype, layout):
     _check(nx, ny, dtype, "solid+force", [3, 8, 5], layout=layout)
 
@@ -102,6 +115,8 @@ def test_sizes_tiled(nx, ny, dtype, layout):
                                      "open+solid+drag+mrt"])
 def test_variants_other_layouts(variant, dtype, layout):
     _check(144, 48, dtype, variant, [7, 10], layout=layout)
+    if dtype != "bf16s":
+        _check(1072, 592, dtype, variant, [11], layout=layout)
 
 
 @pytest.mark.parametrize("layout", ["indirect", "tiled16"])
@@ -109,10 +124,12 @@ def test_sparse_holes(layout):
     """Whole solid squares, rows and strips between the fluid nodes, and one fluid node."""
     import paper_2108_13241_amd as lbm
     announce(f"fused steps, sparse holes, {layout}")
-    m = np.ones((96, 320), dtype=np.uint8)
+    m = np.ones((960, 640), dtype=np.uint8)
+    m[100:900, :] = 0
     m[20:45, 30:90] = 0
     m[60:75, 150:320] = 0
-    m[50, 200] = 0
+    m[300:420, 100:500] = 1
+    m[350, 200] = 0
     m[0:3, :40] = 0
     lats = [lbm.Lattice(m, 0.8, force=(1e-4, 2e-4), dtype="f64", layout=layout) for _ in range(2)]
     lats[0].step(23)
