@@ -79,6 +79,10 @@ struct lbm_ctx {
     int32_t graph_len = 0;
     hipStream_t capture_stream = nullptr;
     bool no_pair = false;  // AA: the second lattice could not be allocated
+    // A call of this context was captured into a caller's graph: from then on every
+    // step(n) leaves the state in the buffer that n single steps would, so that
+    // the graph finds it there whatever runs between its replays.
+    mutable bool recorded = false;
     // Overlapped checkpointed adjoint: a second segment buffer (library-owned),
     // an auxiliary stream for the segment recomputation and its events.
     void *seg2 = nullptr;
@@ -93,6 +97,14 @@ int fail(lbm_ctx *c, int status, const std::string &msg)
 {
     c->last_error = msg;
     return status;
+}
+
+void note_capture(const lbm_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!c->recorded && c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+        st != hipStreamCaptureStatusNone)
+        c->recorded = true;
 }
 
 int fail_device(lbm_ctx *c, hipError_t e, const char *what)
@@ -115,6 +127,7 @@ int fail_device(lbm_ctx *c, hipError_t e, const char *what)
             return fail_tl(LBM_ERR_INVALID, "context is NULL");                 \
         if ((c)->broken)                                                        \
             return fail((c), LBM_ERR_STATE, "context broken by an earlier error: " + (c)->last_error); \
+        note_capture(c);                                                        \
     } while (0)
 
 void *raw_alloc(const Allocator &a, size_t bytes)
@@ -892,16 +905,14 @@ int lbm_step(lbm_ctx *c, int64_t n)
     }
     if (n == 0)
         return LBM_OK;
-    // While the caller captures the stream into a graph of its own, the launches
-    // have to be repeatable: the AA layout steps in place, the others keep the
-    // parity of the lattice that holds the state.
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    const bool capturing = c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
-                           st != hipStreamCaptureStatusNone;
+    // Where a graph holds this context's buffers, each call ends in the buffer
+    // that single steps would end in: the AA layout steps in place, the others keep
+    // the parity of the lattice that holds the state (their own graphs, one per
+    // lattice, need no such care).
     if (c->s.layout == LBM_DENSE_AA)
-        LBM_HIP(c, step_aa(c, c->s.stream, n, capturing));
+        LBM_HIP(c, step_aa(c, c->s.stream, n, c->recorded || c->graph_len != 0));
     else
-        LBM_HIP(c, step_groups(c, c->s.stream, n, capturing));
+        LBM_HIP(c, step_groups(c, c->s.stream, n, c->recorded));
     return LBM_OK;
 }
 

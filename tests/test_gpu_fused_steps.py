@@ -139,14 +139,15 @@ def test_sparse_holes(layout):
     assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("layout", ["dense_ab", "dense_aa"])
 @pytest.mark.parametrize("graph", [0, 2, 10, 34])
-def test_graph_lengths(graph):
+def test_graph_lengths(graph, layout):
     """Replays of any even length return to the lattice they start from."""
-    announce(f"fused steps, graphs of {graph}")
-    fused, _ = _lattice(200, 60, "f32", "solid+force", 5)
-    single, _ = _lattice(200, 60, "f32", "solid+force", 5)
+    announce(f"fused steps, graphs of {graph}, {layout}")
+    fused, _ = _lattice(200, 60, "f32", "solid+force", 5, layout)
+    single, _ = _lattice(200, 60, "f32", "solid+force", 5, layout)
     fused.set_graph_steps(graph)
-    for n in (35, 1, 69):
+    for n in (35, 1, 69, 14, 36):
         fused.step(n)
         for _ in range(n):
             single.step(1)
@@ -168,3 +169,31 @@ def test_save_state_between_groups():
     fused.save_state(a)
     single.save_state(b)
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("layout", ["dense_ab", "dense_aa", "indirect"])
+@pytest.mark.parametrize("n", [2, 8, 14])
+def test_callers_graph(layout, n):
+    """A caller's graph of step(n), replayed with eager calls of an even number of steps between
+    the replays: it finds the state where it was recorded."""
+    import torch
+    announce(f"fused steps, captured by the caller, {layout} {n}")
+    a, _ = _lattice(150, 50, "f32", "solid+force", 5, layout)
+    b, _ = _lattice(150, 50, "f32", "solid+force", 5, layout)
+    stream = torch.cuda.Stream()
+    a.set_stream(stream)
+    a.step(9)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        a.step(n)  # recorded, not run, and counted
+    total = 9
+    for eager in (8, 2, 22):
+        with torch.cuda.stream(stream):
+            graph.replay()
+        a.step(eager)
+        torch.cuda.synchronize()
+        total += n + eager
+    for _ in range(total):
+        b.step(1)
+    assert np.array_equal(a.get_populations(), b.get_populations())
