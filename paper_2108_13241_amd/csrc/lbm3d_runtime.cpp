@@ -52,9 +52,21 @@ struct lbm3d_ctx {
     int64_t n_fluid = 0;
     bool keep_all = false;  // TILED16_ALL
     double *red_out = nullptr;
+    bool no_pair = false;  // AA: the second lattice could not be allocated
+    // A call of this context was captured into a caller's graph: from then on every
+    // step(n) leaves the state in the buffer that n single steps would.
+    mutable bool recorded = false;
 };
 
 namespace {
+
+void note_capture(const lbm3d_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (!c->recorded && c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+        st != hipStreamCaptureStatusNone)
+        c->recorded = true;
+}
 
 int fail(lbm3d_ctx *c, int status, const std::string &msg)
 {
@@ -83,6 +95,7 @@ int fail_device(lbm3d_ctx *c, hipError_t e, const char *what)
         if ((c)->broken)                                                                     \
             return fail((c), LBM_ERR_STATE,                                                  \
                         "context broken by an earlier error: " + (c)->last_error);           \
+        note_capture(c);                                                                     \
     } while (0)
 
 void *raw_alloc(const lbm3d_ctx *c, size_t bytes)
@@ -437,16 +450,73 @@ int lbm3d_set_bounce_back(lbm3d_ctx *c, int32_t mode)
     return LBM_OK;
 }
 
+// Largest second lattice the AA layout allocates for pairs of steps; larger
+// lattices are stepped in place.
+constexpr size_t kPairBudget3 = size_t(2) << 30;
+
+// Whether pairs of steps run on this context (AA: its second lattice is allocated
+// on the first call; none once a caller's graph holds the first).
+static bool ensure_pair_lattice(lbm3d_ctx *c)
+{
+    lbm3::State3 s = c->s;
+    if (s.aa && !s.f[1])
+        s.f[1] = s.f[0];
+    if (!lbm3::pair_supported3(s))
+        return false;
+    if (!c->s.aa)
+        return true;
+    if (c->recorded)
+        return false;
+    if (c->s.f[1])
+        return true;
+    size_t b = 0;
+    if (c->no_pair || lbm3d_state_bytes(c, &b) != LBM_OK || b > kPairBudget3)
+        return false;
+    void *p = own_alloc(c, b);
+    if (!p || lbm3::launch_rest3(c->s, p) != hipSuccess) {  // slots no step writes
+        c->no_pair = true;
+        return false;
+    }
+    c->s.f[1] = p;
+    return true;
+}
+
 int lbm3d_step(lbm3d_ctx *c, int64_t n)
 {
     LBM3_CHECK_CTX(c);
     if (n < 0)
         return fail(c, LBM_ERR_INVALID, "n must be >= 0");
-    for (int64_t k = 0; k < n; ++k) {
+    auto single = [&]() -> int {
         LBM3_HIP(c, lbm3::launch_step3(c->s, c->cur));
         c->cur ^= 1;
         ++c->t;
+        --n;
+        return LBM_OK;
+    };
+    // Pairs of steps where the layout has them.  A pair leaves the state of an A-B
+    // context in the other lattice, as one step does; the AA layout takes pairs from
+    // an odd number of steps on, into its second lattice (parity kept).
+    const bool aa = c->s.aa != 0;
+    if (n >= 2 && ensure_pair_lattice(c)) {
+        if (aa && c->cur == 0)
+            if (int rc = single())
+                return rc;
+        int64_t pairs = n / 2;
+        if (c->recorded && (pairs & 1))
+            --pairs;  // two single steps instead: as many launches as steps, modulo 2
+        for (; pairs > 0; --pairs) {
+            LBM3_HIP(c, lbm3::launch_pair3(c->s, c->cur));
+            if (aa)
+                std::swap(c->s.f[0], c->s.f[1]);
+            else
+                c->cur ^= 1;
+            c->t += 2;
+            n -= 2;
+        }
     }
+    while (n > 0)
+        if (int rc = single())
+            return rc;
     return LBM_OK;
 }
 
