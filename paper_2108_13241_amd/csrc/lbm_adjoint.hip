@@ -13,6 +13,7 @@
 // Gradients accumulate in FP64; the per-block dJ/dg partials are summed in a
 // fixed order, so results are repeatable.
 #include <mutex>
+#include <type_traits>
 
 #include "lbm_device.h"
 #include "lbm_launch.h"
@@ -244,6 +245,127 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_step(
     }
 }
 
+// K reverse steps of a small lattice in one launch.  One step is a launch of a few
+// microseconds that waits on the one before, and the least of its time is
+// arithmetic; here a workgroup owns an N x N square of nodes, one per lane, keeps the
+// adjoint field in LDS (two copies, one barrier per step) and the gradients in
+// registers, and reads only the state of each step.  The square loses a ring of nodes
+// per step; its (N - 2 K)^2 inner nodes write the adjoint field and the gradients,
+// whose sums add the steps in the order of single launches.  Now the latency of one
+// workgroup per CU bounds it (90 VGPRs in FP32; at two per CU it spills, 17 us per step
+// at 1024 x 256 against 10; loading the states two steps ahead changed nothing).
+// Backward pass with the recomputation beside it, us per step, single launches ->
+// squares: FP32 1024 x 256 12.4 -> 10.4, 400 x 150 7.0 -> 4.6, 900^2 33 -> 30; FP64 1024
+// x 256 22 -> 17, 200 x 60 7.5 -> 5.0, 900^2 56 -> 51.
+// States: number 0 at `first`, number j > 0 at rest + j * every; the steps take
+// numbers j0, j0 - 1, .. j0 - K + 1.
+template <class ST, bool DRAG, int N, int WAVES>
+__global__ __launch_bounds__(N *N, WAVES) void k_adjoint_square(
+    const typename ST::mem *__restrict__ first, const typename ST::mem *__restrict__ rest,
+    uint64_t every, int j0, int K, const typename ST::real *__restrict__ mu_in,
+    typename ST::real *__restrict__ mu_out, const uint8_t *__restrict__ type,
+    const uint8_t *__restrict__ nmask, const float *__restrict__ alpha,
+    double *__restrict__ grad_alpha, double *__restrict__ partials, int nx, int ny, int pitch,
+    uint32_t nbx, typename ST::real omega, typename ST::real gx, typename ST::real gy)
+{
+    using R = typename ST::real;
+    using M = typename ST::mem;
+    constexpr int kPad = N + 1, kPlane = N * N + 2 * kPad;
+    __shared__ R ring[2][9][kPlane];
+    const int out = N - 2 * K;
+    const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const int by = (int)(b / nbx), bx = (int)(b - (uint32_t)by * nbx);
+    const int tx = (int)threadIdx.x % N, ty = (int)threadIdx.x / N;
+    const int xu = bx * out - K + tx, yu = by * out - K + ty;  // before the periodic wrap
+    int x = xu % nx, y = yu % ny;
+    x = x < 0 ? x + nx : x;
+    y = y < 0 ? y + ny : y;
+    const uint32_t own = (uint32_t)y * (uint32_t)pitch + (uint32_t)x;
+    const uint8_t t = type[own];
+    const unsigned sm = solid_bits(t, nmask, own);
+    const bool keep = tx >= K && tx < N - K && ty >= K && ty < N - K && xu < nx && yu < ny &&
+                      t != kSolid;
+    const R al = DRAG ? (R)alpha[own] : R(0);
+    // element offsets (a lattice small enough for squares has fewer than 2^31)
+    const DenseRC a = dense_rc(x, y, nx, ny, (uint32_t)pitch / kChunk);
+    const uint32_t r[3] = {(uint32_t)a.r[0], (uint32_t)a.r[1], (uint32_t)a.r[2]};
+    const uint32_t o = r[1] + a.c[1];
+    uint32_t from[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        // x - c_i solid: the node's own bounce-back slot
+        const uint32_t away = (uint32_t)(i * (int)kChunk) + r[1 - kCy[i]] + a.c[1 - kCx[i]];
+        const uint32_t here = (uint32_t)(kOpp[i] * (int)kChunk) + o;
+        from[i] = ((sm >> i) & 1u) ? here : away;
+    }
+    R mu[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+        mu[i] = mu_in[(uint32_t)(i * (int)kChunk) + o];
+    double ga = 0.0, gxs = 0.0, gys = 0.0;
+    if (DRAG && keep)
+        ga = grad_alpha[(size_t)y * nx + x];
+    const int at = (int)threadIdx.x + kPad;
+    for (int s = 0; s < K; ++s) {
+        R(&m)[9][kPlane] = ring[s & 1];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            m[i][at] = mu[i];
+        const M *st = j0 == s ? first : rest + (uint64_t)(j0 - s) * every;
+        M f[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            f[i] = st[from[i]];
+        lds_barrier();
+        // rows of this wavefront that no later step needs
+        const int lo = __builtin_amdgcn_readfirstlane(ty), hi = lo + 64 / N - 1;
+        if (hi <= s || lo >= N - 1 - s)
+            continue;
+        R h[9], nu[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            h[i] = ST::ld(f[i], i);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            nu[i] = m[i][at + kCx[i] + N * kCy[i]];
+        if (__ballot(sm != 0) != 0) {
+            // x + c_i solid: the adjoint of that bounce-back, mu_opp(i)(x)
+#pragma unroll
+            for (int i = 1; i < 9; ++i)
+                if ((sm >> kOpp[i]) & 1u)
+                    nu[i] = m[kOpp[i]][at];
+        }
+        R ab, gbx, gby;
+        collide_vjp<R, DRAG, ST::kShift>(h, nu, omega, gx, gy, al, mu, ab, gbx, gby);
+        if (keep) {
+            ga += (double)ab;
+            gxs += (double)gbx;
+            gys += (double)gby;
+        }
+    }
+    if (keep) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            mu_out[(uint32_t)(i * (int)kChunk) + o] = mu[i];
+        if (DRAG)
+            grad_alpha[(size_t)y * nx + x] = ga;
+    }
+    // one dJ/dg partial pair per workgroup
+    wave_sum2(gxs, gys);
+    double *ws = reinterpret_cast<double *>(&ring[K & 1][0][0]);  // not read any more
+    if ((threadIdx.x & 63u) == 0) {
+        ws[2 * (threadIdx.x >> 6)] = gxs;
+        ws[2 * (threadIdx.x >> 6) + 1] = gys;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double sum = partials[2 * b + threadIdx.x];
+        for (int w = 0; w < N * N / 64; ++w)
+            sum += ws[2 * w + (int)threadIdx.x];
+        partials[2 * b + threadIdx.x] = sum;
+    }
+}
+
 // lambda_T = scale * d(sum over column x_col of u_x)/df at the canonical state
 // pulled from the stored lattice, zero elsewhere; direct alpha / g terms too.
 template <class ST>
@@ -398,7 +520,78 @@ hipError_t step_typed(const DevState &s, const void *state, const void *mu_in, v
     return hipGetLastError();
 }
 
+// Side of the squares of k_adjoint_square.
+constexpr int kSquare = 32;
+
+template <class ST>
+hipError_t steps_typed(const DevState &s, const void *first, const void *rest, size_t every, int j0,
+                       int steps, const void *mu_in, void *mu_out, double *grad_alpha,
+                       double *partials)
+{
+    using R = typename ST::real;
+    using M = typename ST::mem;
+    const int out = kSquare - 2 * steps;
+    const uint32_t nbx = (uint32_t)((s.nx + out - 1) / out);
+    const uint32_t blocks = nbx * (uint32_t)((s.ny + out - 1) / out);
+    const R om = (R)s.omega, gx = (R)s.gx, gy = (R)s.gy;
+    constexpr int kWaves = 4;  // per SIMD: one workgroup per CU
+    auto launch = [&](auto drag) {
+        k_adjoint_square<ST, decltype(drag)::value, kSquare, kWaves>
+            <<<blocks, kSquare * kSquare, 0, s.stream>>>(
+                (const M *)first, (const M *)rest, every, j0, steps, (const R *)mu_in, (R *)mu_out,
+                s.type, s.nmask, s.alpha, grad_alpha, partials, s.nx, s.ny, s.pitch, nbx, om, gx,
+                gy);
+    };
+    if (s.alpha)
+        launch(std::true_type{});
+    else
+        launch(std::false_type{});
+    return hipGetLastError();
+}
+
 }  // namespace
+
+// The longest launch of up to five steps whose squares fit the chip in one round (one
+// workgroup per CU), four steps on larger lattices.  Measured at 3 / 4 / 5 / 6 steps, us
+// per step in FP32: 400 x 150 5.2 / 5.1 / 4.6 / 5.2, 700 x 200 6.2 / 6.9 / 7.0 / 6.8, 1024 x
+// 256 11.0 / 10.4 / 11.3 / 11.7, 900^2 29.9 / 30.3 / 31.9 / 33.3.
+int adjoint_square_steps(const DevState &s)
+{
+    int n = 0;
+    if (!square_steps(s.nx, s.ny, s.dtype, n))
+        return 1;
+    for (int k = 5; k >= 3; --k) {
+        const int out = kSquare - 2 * k;
+        if ((int64_t)((s.nx + out - 1) / out) * ((s.ny + out - 1) / out) <= 256)
+            return k;
+    }
+    return 4;
+}
+
+int64_t adjoint_run_partials(const DevState &s)
+{
+    const int k = adjoint_square_steps(s);
+    int64_t n = adjoint_step_partials(s);
+    // the fewest nodes per square are written by the longest launch
+    if (const int out = kSquare - 2 * k; k > 1)
+        n = std::max(n, (int64_t)((s.nx + out - 1) / out) * ((s.ny + out - 1) / out));
+    return n;
+}
+
+hipError_t launch_adjoint_steps_raw(const DevState &s, const void *first, const void *rest,
+                                    size_t every, int j0, int steps, const void *mu_in,
+                                    void *mu_out, double *grad_alpha, double *partials)
+{
+    if (steps < 2 || steps > adjoint_square_steps(s) || steps > j0 + 1)
+        return hipErrorInvalidValue;
+    if (s.dtype == kF64)
+        return steps_typed<F64>(s, first, rest, every, j0, steps, mu_in, mu_out, grad_alpha,
+                                partials);
+    if (s.dtype == kF32)
+        return steps_typed<F32>(s, first, rest, every, j0, steps, mu_in, mu_out, grad_alpha,
+                                partials);
+    return hipErrorInvalidValue;
+}
 
 int64_t adjoint_blocks(const DevState &s)
 {
@@ -409,7 +602,7 @@ int64_t adjoint_step_partials(const DevState &s) { return adjoint_blocks(s) * (k
 
 int64_t adjoint_scratch_pairs(const DevState &s)
 {
-    const int64_t n = std::max(adjoint_step_partials(s), adjoint_seed_blocks(s));
+    const int64_t n = std::max(adjoint_run_partials(s), adjoint_seed_blocks(s));
     return n + (n + kSumPer - 1) / kSumPer + 1;
 }
 

@@ -721,6 +721,14 @@ __device__ __forceinline__ M &dense_at(M *__restrict__ s, const DenseRC &a, int 
     return p[a.c[ci]];
 }
 
+// Barrier that orders LDS only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <class T>
 __device__ __forceinline__ void store_nt(T *p, T v)
 {

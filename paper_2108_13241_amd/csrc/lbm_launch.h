@@ -62,6 +62,9 @@ struct DevState {
     double s_e = 1.0, s_eps = 1.0, s_q = 1.0;  // its energy, energy-square, flux rates
     int64_t n_tiles = 0, n_fluid = 0;
     double omega = 1.0, gx = 0.0, gy = 0.0;
+    // launch_steps on squares: the lattice of every step is stored, this many elements
+    // apart, the first one at f[1 - cur] (0: the last step's only)
+    size_t every = 0;
     hipStream_t stream = nullptr;
     double *red_partials = nullptr;   // reduction scratch (>= red_capacity doubles)
     int64_t red_capacity = 0;
@@ -169,6 +172,16 @@ hipError_t launch_adjoint_seed_raw(const DevState &s, const void *state, int x_c
 hipError_t launch_adjoint_step_raw(const DevState &s, const void *state, const void *mu_in,
                                    void *mu_out, double *grad_alpha, double *partials,
                                    int accumulate);
+// Most reverse steps a launch_adjoint_steps_raw call takes on this lattice (1: none).
+int adjoint_square_steps(const DevState &s);
+// `steps` reverse steps over the states number j0, j0 - 1, .. (number 0 at `first`,
+// j > 0 at rest + j * every elements), with accumulate = 1; per node bitwise those of
+// single steps.
+hipError_t launch_adjoint_steps_raw(const DevState &s, const void *first, const void *rest,
+                                    size_t every, int j0, int steps, const void *mu_in,
+                                    void *mu_out, double *grad_alpha, double *partials);
+// dJ/dg partial pairs of a run of reverse steps, single or several per launch.
+int64_t adjoint_run_partials(const DevState &s);
 // Adjoint field <-> device FP64 planes [9][ny][nx] (to_plain = 1: field -> planes).
 hipError_t launch_adjoint_convert(const DevState &s, void *mu, double *plain, int to_plain);
 // grad_g[0..1] += fixed-order sum of n partial pairs.

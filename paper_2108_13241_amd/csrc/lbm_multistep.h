@@ -57,6 +57,7 @@ struct StripGeom {
     const uint16_t *info;
     const int32_t *tile_of;
     uint32_t n_fluid;
+    uint64_t every;  // squares: DevState::every
 };
 
 // Slot of direction i among those of equal c_i.y (rows kept in registers).
@@ -78,14 +79,6 @@ __device__ __forceinline__ M select_bits(M a, M b, uint32_t m)
         const uint32_t x = __builtin_bit_cast(uint16_t, a), y = __builtin_bit_cast(uint16_t, b);
         return __builtin_bit_cast(M, (uint16_t)((y & m) | (x & ~m)));
     }
-}
-
-// Barrier that orders LDS only: global loads and stores stay in flight.
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // LDS layout of a strip: rows between groups, then node types and drag
@@ -501,6 +494,13 @@ __global__ __launch_bounds__(N *N) void k_steps_square(const DenseArgs<ST> k, co
             open_values<R, ST::kShift>(code, k.bc_val[2 * (size_t)n], k.bc_val[2 * (size_t)n + 1],
                                        b0, b1);
     }
+    auto store = [&](uint64_t d) {
+        if (keep && type != kSolid) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i)
+                k.dst[d + (uint64_t)((PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS) + o] = v[i];
+        }
+    };
     const int at = (int)threadIdx.x + L::kPad;
     for (int t = 0; t < K; ++t) {
         M(&r)[9][L::kPlane] = ring[t & 1];
@@ -526,12 +526,10 @@ __global__ __launch_bounds__(N *N) void k_steps_square(const DenseArgs<ST> k, co
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             v[i] = ST::st(f[i], i);
+        if (g.every && t < K - 1)
+            store((uint64_t)t * g.every);
     }
-    if (keep && type != kSolid) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            k.dst[(uint64_t)((PLACE == kDenseOpp ? kOpp[i] : i) * (int)DS) + o] = v[i];
-    }
+    store((uint64_t)(K - 1) * g.every);
 }
 
 // ---------------------------------------------------------------- dispatch --
@@ -621,6 +619,7 @@ void steps_launch(const DevState &s, int cur, int K)
     g.tile_of = s.tile_of;
     g.n_fluid = (uint32_t)s.n_fluid;
     g.steps = K;
+    g.every = s.every;
     int square = 0;
     square_steps(s.nx, s.ny, s.dtype, square);
     if (square) {

@@ -1295,11 +1295,20 @@ static int recompute_segment(lbm_ctx *c, lbm::DevState &r, const void *ckpt_dev,
 {
     const int64_t t0 = seg * K, len = std::min<int64_t>(K, T - t0);
     st[0] = (const char *)ckpt_dev + (size_t)seg * sb;
-    for (int64_t j = 1; j < len; ++j) {
+    for (int64_t j = 1; j < len; ++j)
         st[j] = (const char *)buf + (size_t)j * sb;
+    // lattices small enough for squares store every step of a launch
+    int square = 0;
+    const int64_t kmax = lbm::square_steps(r.nx, r.ny, r.dtype, square) && r.fluid_frac > 0.0
+                             ? lbm::max_fused_steps(r)
+                             : 1;
+    r.every = sb / (size_t)c->pop_bytes;
+    for (int64_t j = 1; j < len;) {
         r.f[0] = const_cast<void *>(st[j - 1]);
         r.f[1] = const_cast<void *>(st[j]);
-        LBM_HIP(c, lbm::launch_step(r, t0 + j - 1, 0));
+        const int64_t k = std::min(len - j, kmax);
+        LBM_HIP(c, k > 1 ? lbm::launch_steps(r, 0, (int)k) : lbm::launch_step(r, t0 + j - 1, 0));
+        j += k;
     }
     return LBM_OK;
 }
@@ -1325,8 +1334,9 @@ int lbm_adjoint_checkpointed(lbm_ctx *c, int64_t T, int64_t K, const void *ckpt_
     lbm_state_bytes(c, &sb);
     if ((rc = seed_impl(c, state_lattice(c), x_col, dJ, c->mu_buf[0], grad_alpha_dev, grad_g_dev)))
         return rc;
-    const int64_t nb = lbm::adjoint_step_partials(c->s);
+    const int64_t nb = lbm::adjoint_run_partials(c->s);
     LBM_HIP(c, lbm::launch_zero(c->adj_partials, 2 * nb, c->s.stream));
+    const int64_t kmax = lbm::adjoint_square_steps(c->s);
     int mu = 0;
     // Replay state: a copy of the device description whose lattices point into
     // the checkpoint and segment buffers; the context's own lattices (the
@@ -1335,10 +1345,17 @@ int lbm_adjoint_checkpointed(lbm_ctx *c, int64_t T, int64_t K, const void *ckpt_
     const int64_t nseg = (T + K - 1) / K;
     auto adjoint_segment = [&](const std::vector<const void *> &st, int64_t seg) -> int {
         const int64_t len = std::min<int64_t>(K, T - seg * K);
-        for (int64_t j = len - 1; j >= 0; --j) {
-            LBM_HIP(c, lbm::launch_adjoint_step_raw(c->s, st[j], c->mu_buf[mu], c->mu_buf[1 - mu],
-                                                    grad_alpha_dev, c->adj_partials, 1));
+        const char *rest = len > 1 ? (const char *)st[1] - sb : nullptr;
+        for (int64_t j = len - 1; j >= 0;) {
+            const int64_t k = std::min(j + 1, kmax);
+            LBM_HIP(c, k > 1 ? lbm::launch_adjoint_steps_raw(
+                                   c->s, st[0], rest, sb / (size_t)c->pop_bytes, (int)j, (int)k,
+                                   c->mu_buf[mu], c->mu_buf[1 - mu], grad_alpha_dev, c->adj_partials)
+                             : lbm::launch_adjoint_step_raw(c->s, st[j], c->mu_buf[mu],
+                                                            c->mu_buf[1 - mu], grad_alpha_dev,
+                                                            c->adj_partials, 1));
             mu ^= 1;
+            j -= k;
         }
         return LBM_OK;
     };
