@@ -1489,6 +1489,48 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
     return hipErrorInvalidValue;
 }
 
+// Whether fused steps are faster than single ones where the lattice takes squares of
+// several rounds (k steps in `blocks` of them) or strips (k = 0).  A fused launch computes
+// every mesh node, and more for the halo; a single step of a sparse layout touches the
+// fluid nodes only, and below some millions of nodes reads them from the memory-side
+// cache.  So the fewer bytes a node has and the more its collision costs, the later
+// fusing pays.  Measured, us per step, single / fused (discs, with a force):
+//   INDIRECT, fluid fraction 0.4 and 0.6: FP64 640^2 5.7 / 6.3 and 9.9 / 6.4 (0.68), 4096^2
+//   118 / 131 (0.2: 89 / 118) and 217 / 122; FP32 640^2 3.9 / 4.3 and 5.0 / 4.4 (0.68),
+//   896^2 5.1 / 7.4 and 7.5 / 7.5, 4096^2 113 / 97 (0.5); MRT 896^2 7.9 / 9.6 (0.6), 13.1 /
+//   9.8 (0.95), 2048^2 34 / 45 and 44 / 45 (0.8); 16 bits 400^2 3.8 / 2.9, 640^2 3.9 / 4.3,
+//   896^2 7.0 / 7.8 (0.8), 1200^2 12.1 / 13.0 (0.8), 14.4 / 13.0 (0.95), 3008^2 47 / 48 and 61 /
+//   60 (0.8), 4096^2 140 / 104 (0.9), MRT 1200^2 13.1 / 18.2 (0.8).
+//   TILED16 is alike.
+//   Dense, 16 bits: 896^2 with a force 7.2 / 8.5, 640^2 5.4 / 4.5; MRT and force 2048^2 32 /
+//   39, MRT 1200^2 11.0 / 12.2 (AA); open boundaries 1200^2 10.8 / 15.5 (AA), 14.6 / 15.1.  AA
+//   in FP64 with open boundaries 640^2 9.5 / 10.4.
+static bool fused_pays(const DevState &s, int k, int64_t blocks)
+{
+    constexpr double kNever = 2.0;
+    const bool list = s.layout == kIndirect, sparse = list || s.layout == kTiled16;
+    const bool f64 = s.dtype == kF64, f32 = s.dtype == kF32;
+    const bool few = k && blocks <= 512, force = s.gx != 0.0 || s.gy != 0.0;
+    const int64_t nodes = (int64_t)s.nx * s.ny;
+    if (sparse) {
+        double least;  // fluid fraction
+        if (f64)
+            least = few ? 0.0 : nodes < 700000 ? 0.5 : list ? 0.32 : 0.34;
+        else if (f32)
+            least = s.mrt ? (few ? 0.6 : 0.85) : few ? 0.0 : k ? 0.65 : 0.45;
+        else
+            least = s.mrt ? kNever : few ? 0.0 : k ? kNever : nodes < 4000000 ? 0.9 : 0.75;
+        return s.fluid_frac >= least;
+    }
+    if (f64)
+        return !(s.layout == kDenseAA && s.open && !k && nodes < 700000);
+    if (f32 || few)
+        return true;
+    if (s.mrt)
+        return !force && nodes >= 6000000;
+    return k ? blocks <= 800 : !s.open || nodes >= 4000000;
+}
+
 int max_fused_steps(const DevState &s)
 {
     // the full-way rule reads the state of two steps back from the other lattice
@@ -1496,19 +1538,15 @@ int max_fused_steps(const DevState &s)
         return 1;
     if (s.fluid_frac == 0.0)
         return 1;
-    int square = 0;
-    if (const int k = square_steps(s.nx, s.ny, s.dtype, square))
+    int n = 0;
+    const int k = square_steps(s.nx, s.ny, s.dtype, n);
+    const int64_t blocks = k ? square_blocks(s.nx, s.ny, n, k) : 0;
+    if (k && blocks <= 256)
         return k;
-    // The fused kernel's time goes with the mesh area, a single sparse step's with the
-    // fluid nodes, and the lines are where they meet.  Measured, 4096^2 discs with a
-    // force, us per step, fused against single: INDIRECT FP64 122 / 217 at fluid
-    // fraction 0.5, 118 / 89 at 0.2; FP32 97 / 113, 96 / 46; 16 bits 104 / 90 at 0.5,
-    // 104 / 140 at 0.9.  TILED16 FP64 146 / 237, 128 / 106; FP32 107 / 123, 98 / 56;
-    // 16 bits 115 / 93 at 0.5, 114 / 145 at 0.9.
-    if (s.layout == kIndirect && s.fluid_frac < (s.dtype == kF64 ? 0.32 : s.dtype == kF32 ? 0.45 : 0.65))
+    if (!fused_pays(s, k, blocks))
         return 1;
-    if (s.layout == kTiled16 && s.fluid_frac < (s.dtype == kF64 ? 0.34 : s.dtype == kF32 ? 0.45 : 0.75))
-        return 1;
+    if (k)
+        return k;
     // StepsShape::kMax
     const bool force = s.gx != 0.0 || s.gy != 0.0;
     const bool sparse = s.layout == kTiled16 || s.layout == kIndirect;

@@ -81,6 +81,13 @@ int64_t reduction_capacity(const DevState &s);
 // even or odd kernel).
 hipError_t launch_step(const DevState &s, int64_t t, int cur);
 
+// Squares of n x n nodes, which lose a ring of nodes per step, that cover the lattice.
+inline int64_t square_blocks(int nx, int ny, int n, int steps)
+{
+    const int out = n - 2 * steps;
+    return (int64_t)((nx + out - 1) / out) * ((ny + out - 1) / out);
+}
+
 // Small lattices run the fused steps on squares of n x n nodes: n = 16 or 32 and the
 // most steps a launch then takes (returned); n = 0 for larger lattices (strips).
 // 16 x 16 nodes at four steps while that leaves at most one workgroup per CU; else
@@ -94,17 +101,14 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur);
 // strips 5.7, 900^2 6.9, strips 7.5.
 inline int square_steps(int nx, int ny, int dtype, int &n)
 {
-    auto blocks = [&](int out) {
-        return (int64_t)((nx + out - 1) / out) * ((ny + out - 1) / out);
-    };
     n = 16;
-    if (blocks(16 - 2 * 4) <= 256)
+    if (square_blocks(nx, ny, n, 4) <= 256)
         return 4;
     n = 32;
     for (int k = 8; k > 4; --k)
-        if (blocks(32 - 2 * k) <= 256)
+        if (square_blocks(nx, ny, n, k) <= 256)
             return k;
-    if (blocks(32 - 2 * 4) <= (dtype == kF64 ? 512 : 1500))
+    if (square_blocks(nx, ny, n, 4) <= (dtype == kF64 ? 512 : 1500))
         return 4;
     n = 0;
     return 0;

@@ -18,12 +18,12 @@ SIZES = [(1, 1), (5, 3), (48, 17), (57, 2), (111, 9), (112, 40), (113, 33), (241
 DTYPES = ["f64", "f32", "f16s", "bf16s"]
 
 
-def _lattice(nx, ny, dtype, variant, seed, layout="dense_ab"):
+def _lattice(nx, ny, dtype, variant, seed, layout="dense_ab", solid=0.1):
     import paper_2108_13241_amd as lbm
     import synthetic
     kinds = variant.split("+")
     walls = "solid" in kinds
-    m = (synthetic.random_mask(nx, ny, seed=seed, solid_fraction=0.1, walls=ny > 4)
+    m = (synthetic.random_mask(nx, ny, seed=seed, solid_fraction=solid, walls=ny > 4)
          if walls else synthetic.all_fluid(nx, ny))
     g = (2e-4, -1e-4) if "force" in kinds or "drag" in kinds else (0.0, 0.0)
     lat = lbm.Lattice(m, 0.7, force=g, dtype=dtype, layout=layout)
@@ -197,3 +197,40 @@ def test_callers_graph(layout, n):
     for _ in range(total):
         b.step(1)
     assert np.array_equal(a.get_populations(), b.get_populations())
+
+
+def _check_state(nx, ny, dtype, variant, layout, counts, solid=0.05):
+    import torch
+    announce(f"fused steps {nx}x{ny} {dtype} {layout} {variant} {counts}")
+    fused, _ = _lattice(nx, ny, dtype, variant, 21, layout, solid)
+    single, _ = _lattice(nx, ny, dtype, variant, 21, layout, solid)
+    a, b = (torch.zeros(fused.state_bytes(), dtype=torch.uint8, device="cuda") for _ in range(2))
+    for n in counts:
+        fused.step(n)
+        for _ in range(n):
+            single.step(1)
+        fused.save_state(a)
+        single.save_state(b)
+        assert torch.equal(a, b), n
+    fused.close()
+    single.close()
+
+
+@pytest.mark.parametrize("layout", ["dense_ab", "dense_aa", "indirect", "tiled16"])
+@pytest.mark.parametrize("variant", ["solid+force", "solid+trt", "solid+mrt", "solid+drag", "open"])
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16s"])
+def test_strips(dtype, variant, layout):
+    """Lattices just beyond those that run on squares."""
+    if layout == "dense_aa" and "drag" in variant:
+        variant = "force"
+    _check_state(1216, 912, dtype, variant, layout, (13, 8))
+    if layout != "tiled16":
+        _check_state(40011, 9, dtype, variant, layout, (9,))
+
+
+@pytest.mark.parametrize("layout,variant", [("indirect", "solid+force"), ("tiled16", "solid"),
+                                            ("dense_ab", "mrt"), ("dense_aa", "open")])
+@pytest.mark.parametrize("dtype", ["f16s", "bf16s"])
+def test_large_16_bit(dtype, layout, variant):
+    """The 16-bit variants that only large lattices run on strips."""
+    _check_state(2560, 2400, dtype, variant, layout, (11,))
