@@ -1527,7 +1527,7 @@ static bool fused_pays(const DevState &s, int k, int64_t blocks)
     if (f32 || few)
         return true;
     if (s.mrt)
-        return !force && nodes >= 6000000;
+        return !force && !s.alpha && nodes >= 6000000;
     return k ? blocks <= 800 : !s.open || nodes >= 4000000;
 }
 

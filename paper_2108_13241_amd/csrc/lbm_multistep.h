@@ -1,4 +1,5 @@
-// Several D2Q9 steps in one launch (dense A-B layout).
+// Several D2Q9 steps in one launch, on the dense lattices (A-B; AA after an odd number of
+// steps), the node list and the tiles.
 //
 // A single step reads and writes every population once, so it cannot run
 // faster than the memory moves 18 populations a node.  k_steps reads a strip of
@@ -19,10 +20,14 @@
 // steps.  Boundary nodes: the node types travel with the rows; a row of interior
 // nodes (one ballot) skips the bounce-back selects.
 //
-// Measured, Taylor-Green 4096^2, us per step (K single launches before): FP64
-// 400 -> 105 (8 steps), FP32 192 -> 50, FP16 103 -> 47; with node types 110, 54,
-// 51.  The FP32 and 16-bit kernels are then bound by VALU issue (95 % of it at
-// FP32), FP64 by both memory (0.65 of its rate) and VALU.  A form that kept all K
+// Measured, Taylor-Green 4096^2, us per step over calls of 48 steps (single
+// launches -> fused): FP64 390 -> 109 (8 steps a launch), FP32 190 -> 57, FP16 99 ->
+// 59, BF16 99 -> 64; with walls 114, 63, 59, 68; with a force 122, 88, 86, 92; MRT 111,
+// 83, 94, 100.  The FP32 and 16-bit kernels are bound by VALU issue (all of it:
+// 118 and 130 instructions a node and step, 4 cycles a wavefront each).  FP64 moves 2.5 GB a
+// launch (1.03 of one step's) in 860 us, 0.46 of the copy rate, and issues 54 % of the
+// VALU cycles: what is left is the barrier per row, which keeps the two from
+// overlapping fully.  A form that kept all K
 // steps in one wavefront (rows in registers, lane shifts instead of LDS) ran
 // FP64 125, FP32 68, FP16 75 at its best K = 4, 4, 2: K is bounded by the
 // registers there, and boundary handling spilled them.
@@ -632,16 +637,22 @@ void steps_launch(const DevState &s, int cur, int K)
             k_steps_square<ST, PH, PLACE, 32><<<blocks, 1024, 0, s.stream>>>(k, g);
         return;
     }
-    g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
-    const int out = L::kWid - 2 * g.halo;
-    g.nstrips = (uint32_t)((s.nx + out - 1) / out);
-    const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged, (PH & kOpenBC) != 0,
-                                  PLACE);
-    const int per_cu = std::max(1, std::min((int)(163840u / lds), Sh::kWaves * 4 / (S * K)));
-    g.rows = strip_rows(s.ny, g.nstrips, K, per_cu);
-    const uint32_t blocks = g.nstrips * (uint32_t)((s.ny + g.rows - 1) / g.rows);
-    k_steps<ST, PH, WALLS, PLACE, S, Sh::kMax, Sh::kWaves>
-        <<<blocks, (uint32_t)(64 * S * K), lds, s.stream>>>(k, g);
+    // MRT costs the 16-bit types more than its strips save (max_fused_steps): sparse
+    // layouts, and dense ones with a force, take them on squares only
+    constexpr bool kStrips = sizeof(M) > 2 || (PH & kMRT) == 0 ||
+                             (PLACE < kList && (PH & 3) == kBGK);
+    if constexpr (kStrips) {
+        g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
+        const int out = L::kWid - 2 * g.halo;
+        g.nstrips = (uint32_t)((s.nx + out - 1) / out);
+        const uint32_t lds = L::bytes(K, WALLS, (PH & 3) == kDragged, (PH & kOpenBC) != 0,
+                                      PLACE);
+        const int per_cu = std::max(1, std::min((int)(163840u / lds), Sh::kWaves * 4 / (S * K)));
+        g.rows = strip_rows(s.ny, g.nstrips, K, per_cu);
+        const uint32_t blocks = g.nstrips * (uint32_t)((s.ny + g.rows - 1) / g.rows);
+        k_steps<ST, PH, WALLS, PLACE, S, Sh::kMax, Sh::kWaves>
+            <<<blocks, (uint32_t)(64 * S * K), lds, s.stream>>>(k, g);
+    }
 }
 
 template <class ST, int COLL, int PLACE>
