@@ -63,7 +63,9 @@ typedef enum {
  *  DENSE_AA : one full lattice updated in place with the AA access pattern
  *             (the single-copy scheme Sec. 3 mentions): even steps read and
  *             write each node's own slots, odd steps read from and write to the
- *             neighbours.
+ *             neighbours.  Calls of several steps use a second lattice, allocated
+ *             on the first such call, if it takes no more than 2 GiB and can be
+ *             allocated; else, and for captured contexts, all steps run in place.
  *  TILED16  : two lattices holding only the non-empty 16 x 16 tiles, compacted
  *             in row-major tile order (each tile stores its 9 populations as 9
  *             runs of 256), with a tile-neighbour table ("pointer tile" of
@@ -231,15 +233,21 @@ int lbm_set_bounce_back(lbm_ctx *ctx, int32_t mode);
 /* Replace the body force (host double[2], finite). */
 int lbm_set_force(lbm_ctx *ctx, const double *force);
 
-/* Enqueue n >= 0 time steps (Algorithm 1, one fused stream-collide kernel per
- * step).  Asynchronous: returns once enqueued. */
+/* Enqueue n >= 0 time steps (Algorithm 1).  Where it is faster, one kernel takes
+ * up to eight steps (halfway bounce-back; the choice goes by layout, size, type,
+ * collision and fluid fraction); results are bitwise those of n calls of one step,
+ * which run one fused stream-collide kernel each.  Once a call on this context has
+ * been captured into a caller's graph, every later call leaves the state in the
+ * buffer that single steps would, so that the graph stays valid.  Asynchronous:
+ * returns once enqueued (DENSE_AA: the first call of several steps allocates the
+ * second lattice, see lbm_layout). */
 int lbm_step(lbm_ctx *ctx, int64_t n);
 
 /* Replay steps through HIP graphs: lbm_step then enqueues runs of `steps`
  * consecutive steps as one captured graph (captured once, on a private stream,
  * and replayed on the context's stream; bitwise-identical results).  -1 = auto
- * (32 steps for lattices that move less than 128 MB per step, where host launch
- * overhead is a visible share of a step; else off), 0 = off, or an even count in
+ * (32 steps for lattices that move less than 128 MB per step and run one launch per
+ * step, where host launch overhead is a visible share of a step; else off), 0 = off, or an even count in
  * [2, 4096].  The first replay from each parity captures and instantiates its
  * graph (a one-time cost of a few ms).  Changing the force, the drag field or
  * the open boundaries discards captured graphs. */

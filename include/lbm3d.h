@@ -154,7 +154,12 @@ int lbm3d_set_mrt(lbm3d_ctx *ctx, const double *rates);
  * of two steps back).  Synchronises the stream. */
 int lbm3d_set_bounce_back(lbm3d_ctx *ctx, int32_t mode);
 
-/* Enqueue n >= 0 time steps (one kernel launch each). */
+/* Enqueue n >= 0 time steps.  On the dense layouts (halfway rule) one kernel takes two
+ * steps where that is faster; results are bitwise those of n calls of one step.  Once
+ * a call on this context has been captured into a caller's graph, later calls leave
+ * the state in the buffer that single steps would.  DENSE_AA: the first call of
+ * several steps allocates a second lattice if it takes no more than 2 GiB; else, and
+ * for captured contexts, all steps run in place. */
 int lbm3d_step(lbm3d_ctx *ctx, int64_t n);
 
 /* rho and u = m / rho + g / 2 (Eq. 2 with the half-force correction) into host

@@ -13,6 +13,7 @@ registered with ``lbm_set_allocator``) and streams (``torch.cuda.current_stream`
 from __future__ import annotations
 
 import ctypes
+import threading
 
 import numpy as np
 
@@ -34,6 +35,28 @@ _hooks = None
 _hook_active = False
 
 
+# Stream that the running call's allocations belong to (unset: torch's current one).
+_owner = threading.local()
+
+
+def _step(lat, step, n):
+    """step(n) of a lattice.  The AA layout may allocate its second lattice in it, and the
+    block has to come from the lattice's stream, which uses it, whatever stream is current."""
+    if lat.layout != "dense_aa":
+        lat._check(step(lat._ctx, int(n)))
+        return
+    import torch
+    s = lat.stream
+    if not isinstance(s, torch.cuda.Stream):
+        raw = int(getattr(s, "cuda_stream", s) or 0)
+        s = torch.cuda.ExternalStream(raw) if raw else torch.cuda.default_stream()
+    _owner.stream = s
+    try:
+        lat._check(step(lat._ctx, int(n)))
+    finally:
+        _owner.stream = None
+
+
 def _install_torch_allocator():
     """Route the library's device allocations through torch's caching allocator."""
     global _hooks, _hook_active
@@ -46,7 +69,8 @@ def _install_torch_allocator():
 
         def _alloc(nbytes, _user):
             try:
-                t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+                with torch.cuda.stream(getattr(_owner, "stream", None)):
+                    t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
             except Exception:  # noqa: BLE001 - report NULL to the library (LBM_ERR_NOMEM)
                 return None
             p = t.data_ptr()
@@ -227,7 +251,7 @@ class Lattice:
         self._check(self._lib.lbm_set_graph_steps(self._ctx, int(steps)))
 
     def step(self, n=1):
-        self._check(self._lib.lbm_step(self._ctx, int(n)))
+        _step(self, self._lib.lbm_step, n)
 
     def macroscopic(self):
         out = [np.zeros((self.ny, self.nx)) for _ in range(3)]
@@ -428,7 +452,7 @@ class Lattice3D:
         self._check(self._lib.lbm3d_set_bounce_back(self._ctx, int(m)))
 
     def step(self, n=1):
-        self._check(self._lib.lbm3d_step(self._ctx, int(n)))
+        _step(self, self._lib.lbm3d_step, n)
 
     def macroscopic(self):
         out = [np.zeros(self.shape) for _ in range(4)]

@@ -234,3 +234,27 @@ def test_strips(dtype, variant, layout):
 def test_large_16_bit(dtype, layout, variant):
     """The 16-bit variants that only large lattices run on strips."""
     _check_state(2560, 2400, dtype, variant, layout, (11,))
+
+
+def test_second_lattice_belongs_to_its_stream(monkeypatch):
+    """The AA layout's second lattice is allocated on the lattice's stream, whatever stream is
+    current where step is called."""
+    import torch
+    announce("fused steps, AA on a stream of its own")
+    side = torch.cuda.Stream()
+    fused, _ = _lattice(150, 50, "f32", "solid+force", 5, "dense_aa")
+    single, _ = _lattice(150, 50, "f32", "solid+force", 5, "dense_aa")
+    fused.set_stream(side)
+    seen, real = [], torch.empty
+
+    def empty(*args, **kwargs):
+        seen.append(torch.cuda.current_stream())
+        return real(*args, **kwargs)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    fused.step(9)
+    monkeypatch.undo()
+    assert seen and all(s == side for s in seen)
+    for _ in range(9):
+        single.step(1)
+    assert np.array_equal(fused.get_populations(), single.get_populations())
