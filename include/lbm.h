@@ -64,8 +64,9 @@ typedef enum {
  *             (the single-copy scheme Sec. 3 mentions): even steps read and
  *             write each node's own slots, odd steps read from and write to the
  *             neighbours.  Calls of several steps use a second lattice, allocated
- *             on the first such call, if it takes no more than 2 GiB and can be
- *             allocated; else, and for captured contexts, all steps run in place.
+ *             on the first such call, if it takes no more than 4 GiB, half of
+ *             the device's memory is free and it can be allocated; else, and for
+ *             captured contexts, all steps run in place.
  *  TILED16  : two lattices holding only the non-empty 16 x 16 tiles, compacted
  *             in row-major tile order (each tile stores its 9 populations as 9
  *             runs of 256), with a tile-neighbour table ("pointer tile" of

@@ -158,8 +158,9 @@ int lbm3d_set_bounce_back(lbm3d_ctx *ctx, int32_t mode);
  * steps where that is faster; results are bitwise those of n calls of one step.  Once
  * a call on this context has been captured into a caller's graph, later calls leave
  * the state in the buffer that single steps would.  DENSE_AA: the first call of
- * several steps allocates a second lattice if it takes no more than 2 GiB; else, and
- * for captured contexts, all steps run in place. */
+ * several steps allocates a second lattice if it takes no more than 4 GiB and half of
+ * the device's memory is free; else, and for captured contexts, all steps run in
+ * place. */
 int lbm3d_step(lbm3d_ctx *ctx, int64_t n);
 
 /* rho and u = m / rho + g / 2 (Eq. 2 with the half-force correction) into host

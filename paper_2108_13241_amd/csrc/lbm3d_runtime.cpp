@@ -52,7 +52,7 @@ struct lbm3d_ctx {
     int64_t n_fluid = 0;
     bool keep_all = false;  // TILED16_ALL
     double *red_out = nullptr;
-    bool no_pair = false;  // AA: the second lattice could not be allocated
+    bool no_pair = false;  // AA: there is no room for a second lattice
     // A call of this context was captured into a caller's graph: from then on every
     // step(n) leaves the state in the buffer that n single steps would.
     mutable bool recorded = false;
@@ -450,10 +450,6 @@ int lbm3d_set_bounce_back(lbm3d_ctx *c, int32_t mode)
     return LBM_OK;
 }
 
-// Largest second lattice the AA layout allocates for pairs of steps; larger
-// lattices are stepped in place.
-constexpr size_t kPairBudget3 = size_t(2) << 30;
-
 // Whether pairs of steps run on this context (AA: its second lattice is allocated
 // on the first call; none once a caller's graph holds the first).
 static bool ensure_pair_lattice(lbm3d_ctx *c)
@@ -470,8 +466,12 @@ static bool ensure_pair_lattice(lbm3d_ctx *c)
     if (c->s.f[1])
         return true;
     size_t b = 0;
-    if (c->no_pair || lbm3d_state_bytes(c, &b) != LBM_OK || b > kPairBudget3)
+    if (c->no_pair || lbm3d_state_bytes(c, &b) != LBM_OK)
         return false;
+    if (!lbm::spare_lattice(b)) {
+        c->no_pair = true;
+        return false;
+    }
     void *p = own_alloc(c, b);
     if (!p || lbm3::launch_rest3(c->s, p) != hipSuccess) {  // slots no step writes
         c->no_pair = true;

@@ -81,6 +81,17 @@ int64_t reduction_capacity(const DevState &s);
 // even or odd kernel).
 hipError_t launch_step(const DevState &s, int64_t t, int cur);
 
+// Whether the AA layout may allocate a second lattice of that many bytes for steps that
+// share a launch: no more than 4 GiB (256^3 in FP64: 890 us per step in place, 534 in
+// pairs), and while at least half of the device's memory is free, so that programs
+// that fill it keep the layout's one lattice.
+inline bool spare_lattice(size_t bytes)
+{
+    size_t free = 0, total = 0;
+    return bytes <= (size_t(4) << 30) && hipMemGetInfo(&free, &total) == hipSuccess &&
+           free >= total / 2;
+}
+
 // Squares of n x n nodes, which lose a ring of nodes per step, that cover the lattice.
 inline int64_t square_blocks(int nx, int ny, int n, int steps)
 {

@@ -78,7 +78,7 @@ struct lbm_ctx {
     hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
     int32_t graph_len = 0;
     hipStream_t capture_stream = nullptr;
-    bool no_pair = false;  // AA: the second lattice could not be allocated
+    bool no_pair = false;  // AA: there is no room for a second lattice
     // A call of this context was captured into a caller's graph: from then on every
     // step(n) leaves the state in the buffer that n single steps would, so that
     // the graph finds it there whatever runs between its replays.
@@ -734,17 +734,13 @@ int lbm_set_force(lbm_ctx *c, const double *force)
     return LBM_OK;
 }
 
-// Largest second lattice the AA layout allocates for its fused steps; larger
-// lattices are stepped in place.
-constexpr size_t kPairBudget = size_t(2) << 30;
-
 // Most steps a launch may take on this context.
 static int fused_limit(const lbm_ctx *c)
 {
     lbm::DevState s = c->s;
     if (s.layout == LBM_DENSE_AA && !s.f[1]) {
         // the second lattice is allocated on the first call that uses it
-        if (c->no_pair || (size_t)9 * s.plane * c->pop_bytes > kPairBudget)
+        if (c->no_pair)
             return 1;
         s.f[1] = s.f[0];
     }
@@ -758,7 +754,7 @@ static int32_t graph_length(const lbm_ctx *c)
 {
     if (c->graph_steps >= 0)
         return c->graph_steps;
-    if (fused_limit(c) > 1)
+    if (fused_limit(c) > 1 && !(c->s.layout == LBM_DENSE_AA && c->recorded))
         return 0;
     const double bytes = 18.0 * (double)c->s.plane * c->pop_bytes;
     return bytes < 128.0 * (1 << 20) ? 32 : 0;
@@ -818,7 +814,7 @@ static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, bool in_pla
     if (!in_place && n - before >= 2 && fused_limit(c) > 1) {
         if (!c->s.f[1]) {
             const size_t b = (size_t)9 * c->s.plane * c->pop_bytes;
-            c->s.f[1] = own_alloc(c, b);
+            c->s.f[1] = lbm::spare_lattice(b) ? own_alloc(c, b) : nullptr;
             c->no_pair = c->s.f[1] == nullptr;
             if (c->s.f[1]) {
                 lbm::DevState s = c->s;
