@@ -195,148 +195,11 @@ __device__ __forceinline__ MrtMoments<R> mrt_moments(const R (&v)[9])
     return m;
 }
 
-// The FP64 collision (called by collide), same update with fewer operations: it is
-// written in the momentum j = rho u (m itself without a force) and forms what the
-// directions of a pair share once.  With
-//   E0 = omega (rho - 1.5 u.j) - 3 (1 - omega/2) u.F,
-//   J  = omega j + 2 (1 - omega/2) F,   K = omega j + (1 - omega/2) F,
-// a pair of weight w becomes
-//   f_{i, opp} <- (1 - omega) f_{i, opp} + [w E0 + 4.5 w (c.u)(c.J)] +- 3 w (c.K);
-// TRT: omega_m in the place of omega in K and on f_i - f_opp.  MRT: the moments of
-// f^eq (Eq. 6) and of Guo's term in closed form instead of the moments of f - f^eq:
-//   e^eq = -2 rho + 3 u.j, eps^eq = rho - 3 u.j, q^eq = -j,
-//   p_xx^eq = u_x j_x - u_y j_y, p_xy^eq = u_x j_y,
-//   S = 6 u.F, -6 u.F, -F, 2 (u_x F_x - u_y F_y), u_x F_y + u_y F_x.
-// About 70 operations a node against 100 (BGK, no force), 85 against 170 (MRT).  A
-// single step is bound by memory either way; the fused steps are not (4096^2
-// Taylor-Green, 8 steps a launch: 117 -> 105 us per step).  Its error against
-// 64-bit reference fields (relative 1e-14 after 50 steps) is that of the general
-// form.  FP64 only: FP32 results keep the rounding of the general form.
-template <bool DRAG, bool FORCE, bool TRT, bool MRT>
-__device__ __forceinline__ void collide64(double (&f)[9], const double omega, const double gx,
-                                          const double gy, const double alpha,
-                                          const Rates<double> &rt)
-{
-    using R = double;
-    const R ax = f[1] + f[3], ay = f[2] + f[4], dp = f[5] + f[7], dm = f[6] + f[8];
-    const R sx = f[1] - f[3], sy = f[2] - f[4];
-    const R d5 = f[5] - f[7], d8 = f[8] - f[6];
-    const R axes = ax + ay, diag = dp + dm;
-    const R sum = f[0] + axes + diag;
-    const R dx = d5 + d8, dy = d5 - d8;
-    const R mx = sx + dx, my = sy + dy;
-    const R inv_rho = recip(sum);
-    R ux = mx * inv_rho, uy = my * inv_rho;
-    R jx = mx, jy = my, Fx = R(0), Fy = R(0);
-    if constexpr (FORCE) {
-        ux += R(0.5) * gx;
-        uy += R(0.5) * gy;
-        Fx = sum * gx;
-        Fy = sum * gy;
-        jx += R(0.5) * Fx;
-        jy += R(0.5) * Fy;
-        if constexpr (DRAG) {
-            const R invD = recip(R(1) + R(0.5) * alpha);
-            ux *= invD;
-            uy *= invD;
-            jx *= invD;
-            jy *= invD;
-            Fx -= alpha * jx;
-            Fy -= alpha * jy;
-        }
-    }
-    const R uj = ux * jx + uy * jy;
-    const R uF = FORCE ? ux * Fx + uy * Fy : R(0);
-    if constexpr (MRT) {
-        auto relax = [](R s, R dk, R sk) {
-            if constexpr (FORCE)
-                return s * dk - (R(1) - R(0.5) * s) * sk;
-            else
-                return s * dk;
-        };
-        const R b = relax(rt.s_e, R(2) * (diag + sum) - (R(4) * f[0] + axes) - R(3) * uj,
-                          R(6) * uF) * R(1.0 / 36.0);
-        const R c = relax(rt.s_eps, (R(4) * f[0] + diag) - (R(2) * axes + sum) + R(3) * uj,
-                          R(-6) * uF) * R(1.0 / 36.0);
-        const R qx = relax(rt.s_q, dx - R(2) * sx + jx, -Fx) * R(1.0 / 12.0);
-        const R qy = relax(rt.s_q, dy - R(2) * sy + jy, -Fy) * R(1.0 / 12.0);
-        const R p = relax(omega, (ax - ay) - (ux * jx - uy * jy), R(2) * (ux * Fx - uy * Fy)) *
-                    R(0.25);
-        const R r = relax(omega, (dp - dm) - ux * jy, ux * Fy + uy * Fx) * R(0.25);
-        const R hx = FORCE ? Fx * R(-1.0 / 6.0) : R(0);
-        const R hy = FORCE ? Fy * R(-1.0 / 6.0) : R(0);
-        // f_i -= sum_k M_ki Delta_k / |M_k|^2 (rows written out per direction)
-        f[0] -= R(4) * (c - b);
-        const R A = -(b + R(2) * c), D = R(2) * b + c;
-        const R X = hx + qx, Y = hy + qy;
-        const R Ap = A + p, Am = A - p;
-        const R ox = hx - R(2) * qx, oy = hy - R(2) * qy;
-        f[1] -= Ap + ox;
-        f[3] -= Ap - ox;
-        f[2] -= Am + oy;
-        f[4] -= Am - oy;
-        const R Dp = D + r, Dm = D - r;
-        const R P = X + Y, Q = Y - X;
-        f[5] -= Dp + P;
-        f[7] -= Dp - P;
-        f[6] -= Dm + Q;
-        f[8] -= Dm - Q;
-        return;
-    }
-    const R keep = R(1) - omega;
-    const R guo = R(1) - R(0.5) * omega;
-    R E0 = omega * (sum - R(1.5) * uj);
-    R Jx = omega * jx, Jy = omega * jy;
-    R Kx, Ky;
-    if constexpr (TRT) {
-        Kx = rt.omega_m * jx;
-        Ky = rt.omega_m * jy;
-    } else {
-        Kx = Jx;
-        Ky = Jy;
-    }
-    if constexpr (FORCE) {
-        const R guo_m = TRT ? R(1) - R(0.5) * rt.omega_m : guo;
-        E0 -= R(3) * (guo * uF);
-        Kx += guo_m * Fx;
-        Ky += guo_m * Fy;
-        const R guo2 = R(2) * guo;
-        Jx += guo2 * Fx;
-        Jy += guo2 * Fy;
-    }
-    Kx *= R(3);
-    Ky *= R(3);
-    const R w9 = R(1.0 / 9.0);
-    const R a = w9 * E0, a4 = R(0.25) * a;
-    f[0] = keep * f[0] + R(4) * a;
-    // f_{i, opp} of a pair with even part e and odd part o
-    auto pair = [&](R &fi, R &fj, R e, R o) {
-        if constexpr (TRT) {
-            const R P = R(0.5) * keep * (fi + fj) + e;
-            const R M = R(0.5) * (R(1) - rt.omega_m) * (fi - fj) + o;
-            fi = P + M;
-            fj = P - M;
-        } else {
-            fi = keep * fi + (e + o);
-            fj = keep * fj + (e - o);
-        }
-    };
-    pair(f[1], f[3], a + R(0.5) * ux * Jx, w9 * Kx);
-    pair(f[2], f[4], a + R(0.5) * uy * Jy, w9 * Ky);
-    const R w36 = R(1.0 / 36.0);
-    pair(f[5], f[7], a4 + R(0.125) * (ux + uy) * (Jx + Jy), w36 * (Kx + Ky));
-    pair(f[6], f[8], a4 + R(0.125) * (uy - ux) * (Jy - Jx), w36 * (Ky - Kx));
-}
-
 template <class R, bool DRAG, bool SHIFT, bool FORCE = true, bool EXACT = true, bool TRT = false,
           bool MRT = false>
 __device__ __forceinline__ void collide(R (&f)[9], const R omega, const R gx, const R gy,
                                         const R alpha, const Rates<R> &rt = Rates<R>{})
 {
-    if constexpr (!SHIFT) {
-        collide64<DRAG, FORCE, TRT, MRT>(f, omega, gx, gy, alpha, rt);
-        return;
-    }
     const R omega_m = rt.omega_m;
     const R sum = f[0] + f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
     const R mx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
