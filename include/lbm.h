@@ -63,10 +63,8 @@ typedef enum {
  *  DENSE_AA : one full lattice updated in place with the AA access pattern
  *             (the single-copy scheme Sec. 3 mentions): even steps read and
  *             write each node's own slots, odd steps read from and write to the
- *             neighbours.  Calls of several steps use a second lattice, allocated
- *             on the first such call, if it takes no more than 4 GiB, half of
- *             the device's memory is free and it can be allocated; else, and for
- *             captured contexts, all steps run in place.
+ *             neighbours.  The context never holds a second lattice; a caller can
+ *             lend one for the duration of a call (lbm_step_scratch).
  *  TILED16  : two lattices holding only the non-empty 16 x 16 tiles, compacted
  *             in row-major tile order (each tile stores its 9 populations as 9
  *             runs of 256), with a tile-neighbour table ("pointer tile" of
@@ -239,10 +237,21 @@ int lbm_set_force(lbm_ctx *ctx, const double *force);
  * collision and fluid fraction); results are bitwise those of n calls of one step,
  * which run one fused stream-collide kernel each.  Once a call on this context has
  * been captured into a caller's graph, every later call leaves the state in the
- * buffer that single steps would, so that the graph stays valid.  Asynchronous:
- * returns once enqueued (DENSE_AA: the first call of several steps allocates the
- * second lattice, see lbm_layout). */
+ * buffer that single steps would, so that the graph stays valid.  DENSE_AA: one
+ * step per launch, in place.  Asynchronous: returns once enqueued. */
 int lbm_step(lbm_ctx *ctx, int64_t n);
+
+/* lbm_step with device memory lent for the call: DENSE_AA then takes several steps
+ * per kernel as the other layouts do, back and forth between its lattice and the
+ * scratch memory, and ends in its own; results are bitwise the same.  The memory needs
+ * no initial value and holds nothing of use afterwards; it has to stay valid, and
+ * unused by others, until the work enqueued on the context's stream is done.
+ * lbm_step_scratch_bytes gives the size that lbm_step_scratch can use for n steps from
+ * the present state: one lattice, or 0 where none helps (other layouts, few steps,
+ * explicit lbm_set_graph_steps) and while the stream is being captured.  scratch NULL,
+ * or no use for it: as lbm_step.  bytes smaller than needed: LBM_ERR_INVALID. */
+int lbm_step_scratch_bytes(lbm_ctx *ctx, int64_t n, size_t *bytes);
+int lbm_step_scratch(lbm_ctx *ctx, int64_t n, void *scratch, size_t bytes);
 
 /* Replay steps through HIP graphs: lbm_step then enqueues runs of `steps`
  * consecutive steps as one captured graph (captured once, on a private stream,

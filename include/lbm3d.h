@@ -157,11 +157,14 @@ int lbm3d_set_bounce_back(lbm3d_ctx *ctx, int32_t mode);
 /* Enqueue n >= 0 time steps.  On the dense layouts (halfway rule) one kernel takes two
  * steps where that is faster; results are bitwise those of n calls of one step.  Once
  * a call on this context has been captured into a caller's graph, later calls leave
- * the state in the buffer that single steps would.  DENSE_AA: the first call of
- * several steps allocates a second lattice if it takes no more than 4 GiB and half of
- * the device's memory is free; else, and for captured contexts, all steps run in
+ * the state in the buffer that single steps would.  DENSE_AA: one step per launch, in
  * place. */
 int lbm3d_step(lbm3d_ctx *ctx, int64_t n);
+
+/* lbm3d_step with device memory lent for the call, as lbm_step_scratch: DENSE_AA then
+ * takes two steps per kernel and ends in its own lattice. */
+int lbm3d_step_scratch_bytes(lbm3d_ctx *ctx, int64_t n, size_t *bytes);
+int lbm3d_step_scratch(lbm3d_ctx *ctx, int64_t n, void *scratch, size_t bytes);
 
 /* rho and u = m / rho + g / 2 (Eq. 2 with the half-force correction) into host
  * FP64 [nz][ny][nx] arrays (any may be NULL); solid nodes get 0.  Synchronises. */

@@ -13,7 +13,6 @@ registered with ``lbm_set_allocator``) and streams (``torch.cuda.current_stream`
 from __future__ import annotations
 
 import ctypes
-import threading
 
 import numpy as np
 
@@ -35,26 +34,59 @@ _hooks = None
 _hook_active = False
 
 
-# Stream that the running call's allocations belong to (unset: torch's current one).
-_owner = threading.local()
+# The largest lattice that AA steps borrow (256^3 in FP64: 890 us per step in place, 534 in
+# pairs), the share of the device's memory that has to be free for it, so that programs
+# that fill the device keep the layout's one lattice, and the size up to which nobody asks.
+_LEND_BYTES = 4 << 30
+_LEND_FREE = 0.5
+_LEND_SMALL = 64 << 20
 
 
-def _step(lat, step, n):
-    """step(n) of a lattice.  The AA layout may allocate its second lattice in it, and the
-    block has to come from the lattice's stream, which uses it, whatever stream is current."""
-    if lat.layout != "dense_aa":
-        lat._check(step(lat._ctx, int(n)))
-        return
+def _spare(nbytes):
+    """Whether the device has memory to spare; blocks that torch holds unused count as free."""
     import torch
-    s = lat.stream
-    if not isinstance(s, torch.cuda.Stream):
-        raw = int(getattr(s, "cuda_stream", s) or 0)
-        s = torch.cuda.ExternalStream(raw) if raw else torch.cuda.default_stream()
-    _owner.stream = s
+    if nbytes <= _LEND_SMALL:
+        return True
+    free, total = torch.cuda.mem_get_info()
+    if free < _LEND_FREE * total:
+        stats = torch.cuda.memory_stats_as_nested_dict()
+        held, used = (stats[k]["all"]["current"] for k in ("reserved_bytes", "allocated_bytes"))
+        free += held - used
+    return nbytes <= _LEND_BYTES and free >= _LEND_FREE * total
+
+
+def _lend(stream, nbytes):
+    """A block of torch's memory on `stream`, or None where there is none to spare."""
+    import torch
+    if nbytes == 0:
+        return None
+    if torch.cuda.current_stream() != stream:
+        with torch.cuda.stream(stream):
+            return _lend(stream, nbytes)
+    if not _spare(nbytes):
+        return None
     try:
-        lat._check(step(lat._ctx, int(n)))
-    finally:
-        _owner.stream = None
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def _torch_stream(stream):
+    """torch's object for a stream given as such, as an address or as 0 / None (default)."""
+    import torch
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    raw = int(getattr(stream, "cuda_stream", stream) or 0)
+    return torch.cuda.ExternalStream(raw) if raw else torch.cuda.default_stream()
+
+
+def _step_aa(lat, n, scratch_bytes, step_scratch):
+    """step(n) of an AA lattice with a second lattice borrowed for the call: torch's memory on
+    the lattice's stream, so that it can be handed on, in stream order, once step returns."""
+    b = ctypes.c_size_t()
+    lat._check(scratch_bytes(lat._ctx, n, ctypes.byref(b)))
+    block = _lend(lat._torch_stream, b.value)
+    lat._check(step_scratch(lat._ctx, n, _ptr(block), b.value if block is not None else 0))
 
 
 def _install_torch_allocator():
@@ -69,8 +101,7 @@ def _install_torch_allocator():
 
         def _alloc(nbytes, _user):
             try:
-                with torch.cuda.stream(getattr(_owner, "stream", None)):
-                    t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+                t = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
             except Exception:  # noqa: BLE001 - report NULL to the library (LBM_ERR_NOMEM)
                 return None
             p = t.data_ptr()
@@ -144,7 +175,11 @@ def _dptr(a):
 
 
 class Lattice:
-    """One D2Q9 lattice on the current GPU (a thin wrapper of lbm_ctx)."""
+    """One D2Q9 lattice on the current GPU (a thin wrapper of lbm_ctx).
+
+    in_place (attribute): whether the AA layout's steps keep to its one lattice.  False, the
+    default with torch_memory, lets a step call of several steps borrow a second one from
+    torch's memory until it returns, where half of the device's memory is free."""
 
     def __init__(self, mask, tau, force=(0.0, 0.0), dtype="f64", layout="dense_ab",
                  stream=None, torch_memory=True):
@@ -158,6 +193,7 @@ class Lattice:
         self.dtype = dtype
         self.layout = layout
         self._lib = load()
+        self.in_place = not torch_memory
         if torch_memory:
             _install_torch_allocator()
         else:
@@ -189,6 +225,7 @@ class Lattice:
         """stream: torch.cuda.Stream, a raw hipStream_t address, or 0 (default stream)."""
         raw = getattr(stream, "cuda_stream", stream)
         self.stream = stream
+        self._torch_stream = _torch_stream(stream)
         self._check(self._lib.lbm_set_stream(self._ctx, ctypes.c_void_p(int(raw or 0))))
 
     # -- state -----------------------------------------------------------------
@@ -251,7 +288,10 @@ class Lattice:
         self._check(self._lib.lbm_set_graph_steps(self._ctx, int(steps)))
 
     def step(self, n=1):
-        _step(self, self._lib.lbm_step, n)
+        if self.layout == "dense_aa" and not self.in_place:
+            _step_aa(self, int(n), self._lib.lbm_step_scratch_bytes, self._lib.lbm_step_scratch)
+        else:
+            self._check(self._lib.lbm_step(self._ctx, int(n)))
 
     def macroscopic(self):
         out = [np.zeros((self.ny, self.nx)) for _ in range(3)]
@@ -377,7 +417,7 @@ class Lattice3D:
     """One D3Q19 lattice on the current GPU (a thin wrapper of lbm3d_ctx): dense A-B, AA,
     fluid-node-list ("indirect") or 4 x 4 x 4-block tiled ("tiled16", "tiled16_all") layout; BGK, TRT or MRT collision with Guo forcing; halfway
     (or, except on AA, full-way) bounce-back.  Arrays are [nz, ny, nx]; canonical populations
-    [19, nz, ny, nx] in the velocity order of include/lbm3d.h."""
+    [19, nz, ny, nx] in the velocity order of include/lbm3d.h.  in_place: as for Lattice."""
 
     def __init__(self, mask, tau, force=(0.0, 0.0, 0.0), dtype="f64", stream=None,
                  torch_memory=True, layout="dense_ab"):
@@ -391,6 +431,7 @@ class Lattice3D:
         self.mask = mask
         self.dtype = dtype
         self._lib = load()
+        self.in_place = not torch_memory
         if torch_memory:
             _install_torch_allocator()
         else:
@@ -421,6 +462,7 @@ class Lattice3D:
     def set_stream(self, stream):
         raw = getattr(stream, "cuda_stream", stream)
         self.stream = stream
+        self._torch_stream = _torch_stream(stream)
         self._check(self._lib.lbm3d_set_stream(self._ctx, ctypes.c_void_p(int(raw or 0))))
 
     def init_equilibrium(self, rho=None, ux=None, uy=None, uz=None):
@@ -452,7 +494,11 @@ class Lattice3D:
         self._check(self._lib.lbm3d_set_bounce_back(self._ctx, int(m)))
 
     def step(self, n=1):
-        _step(self, self._lib.lbm3d_step, n)
+        if self.layout == "dense_aa" and not self.in_place:
+            _step_aa(self, int(n), self._lib.lbm3d_step_scratch_bytes,
+                     self._lib.lbm3d_step_scratch)
+        else:
+            self._check(self._lib.lbm3d_step(self._ctx, int(n)))
 
     def macroscopic(self):
         out = [np.zeros(self.shape) for _ in range(4)]

@@ -61,6 +61,8 @@ SIGNATURES = {
     "lbm_set_bounce_back": (_c.c_int, [_vp, _i32]),
     "lbm_set_force": (_c.c_int, [_vp, _dp]),
     "lbm_step": (_c.c_int, [_vp, _i64]),
+    "lbm_step_scratch_bytes": (_c.c_int, [_vp, _i64, _c.POINTER(_sz)]),
+    "lbm_step_scratch": (_c.c_int, [_vp, _i64, _vp, _sz]),
     "lbm_set_graph_steps": (_c.c_int, [_vp, _i32]),
     "lbm_macroscopic": (_c.c_int, [_vp, _dp, _dp, _dp]),
     "lbm_macroscopic_device": (_c.c_int, [_vp, _vp, _vp, _vp]),
@@ -103,6 +105,8 @@ SIGNATURES = {
     "lbm3d_set_trt": (_c.c_int, [_vp, _c.c_double]),
     "lbm3d_set_bounce_back": (_c.c_int, [_vp, _i32]),
     "lbm3d_step": (_c.c_int, [_vp, _i64]),
+    "lbm3d_step_scratch_bytes": (_c.c_int, [_vp, _i64, _c.POINTER(_sz)]),
+    "lbm3d_step_scratch": (_c.c_int, [_vp, _i64, _vp, _sz]),
     "lbm3d_macroscopic": (_c.c_int, [_vp, _dp, _dp, _dp, _dp]),
     "lbm3d_get_populations": (_c.c_int, [_vp, _dp]),
     "lbm3d_set_populations": (_c.c_int, [_vp, _dp]),

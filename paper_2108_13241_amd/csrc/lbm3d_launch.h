@@ -24,7 +24,7 @@ struct State3 {
     int nx = 0, ny = 0, nz = 0;
     int pitch = 0;                           // nx rounded up to a multiple of 64
     void *f[2] = {nullptr, nullptr};         // the two lattices (A-B); DENSE_AA: f[0], and
-                                             // f[1] once launch_pair3 is used
+                                             // f[1] = memory lent for one call
     int aa = 0;                              // 1: DENSE_AA, one lattice updated in place
     // INDIRECT (list = 1): fluid nodes only, in row-major order; populations
     // [np/64][19][64] (np = n_fluid rounded up to 64); the compact source table
@@ -66,12 +66,13 @@ struct State3 {
 // is local; the runtime flips it after every step as for A-B).  The view,
 // scatter and macro launches read cur the same way.
 hipError_t launch_step3(const State3 &s, int cur);
-// Two steps in one launch, from lattice cur to 1 - cur (DENSE_AA, after an odd number
-// of steps: from f[0] to f[1]), bitwise those of two launch_step3 calls.
+// Two steps in one launch, from lattice `from` to 1 - from (DENSE_AA: after an odd number
+// of steps, f[1] being lent memory), bitwise those of two launch_step3 calls (fluid
+// nodes; the slots of solid nodes are neither read into a result nor written).
 // pair_supported3: whether the lattice has such a launch (dense layouts with two
 // lattices, halfway rule) and it is faster than two.
 bool pair_supported3(const State3 &s);
-hipError_t launch_pair3(const State3 &s, int cur);
+hipError_t launch_pair3(const State3 &s, int from);
 // Equilibrium of device FP64 [nz][ny][nx] fields (NULL: rho = 1, u = 0) into the
 // canonical buffer fc (FP64 [19][nz][ny][pitch]).
 hipError_t launch_equilibrium3(const State3 &s, const double *rho, const double *ux,

@@ -343,12 +343,12 @@ bool pair_supported3(const State3 &s)
     return nodes >= (s.aa ? 1u << 19 : 1u << 18);
 }
 
-hipError_t launch_pair3(const State3 &s, int cur)
+hipError_t launch_pair3(const State3 &s, int from)
 {
     if (!pair_supported3(s))
         return hipErrorInvalidValue;
-    const void *src = s.aa ? s.f[0] : s.f[cur];
-    void *dst = s.aa ? s.f[1] : s.f[1 - cur];
+    const void *src = s.f[from];
+    void *dst = s.f[1 - from];
     switch (s.dtype) {
     case LBM_F64: return pair_typed<F64>(s, src, dst);
     case LBM_F32: return pair_typed<Shifted<float>>(s, src, dst);

@@ -52,7 +52,6 @@ struct lbm3d_ctx {
     int64_t n_fluid = 0;
     bool keep_all = false;  // TILED16_ALL
     double *red_out = nullptr;
-    bool no_pair = false;  // AA: there is no room for a second lattice
     // A call of this context was captured into a caller's graph: from then on every
     // step(n) leaves the state in the buffer that n single steps would.
     mutable bool recorded = false;
@@ -450,40 +449,31 @@ int lbm3d_set_bounce_back(lbm3d_ctx *c, int32_t mode)
     return LBM_OK;
 }
 
-// Whether pairs of steps run on this context (AA: its second lattice is allocated
-// on the first call; none once a caller's graph holds the first).
-static bool ensure_pair_lattice(lbm3d_ctx *c)
+// The lattices that launch_pair3 works on: the two of A-B, or DENSE_AA's one and a lattice
+// the caller lends for the call (null: steps in place).
+static lbm3::State3 pair_state(const lbm3d_ctx *c, void *scratch)
 {
     lbm3::State3 s = c->s;
-    if (s.aa && !s.f[1])
-        s.f[1] = s.f[0];
-    if (!lbm3::pair_supported3(s))
-        return false;
-    if (!c->s.aa)
-        return true;
-    if (c->recorded)
-        return false;
-    if (c->s.f[1])
-        return true;
-    size_t b = 0;
-    if (c->no_pair || lbm3d_state_bytes(c, &b) != LBM_OK)
-        return false;
-    if (!lbm::spare_lattice(b)) {
-        c->no_pair = true;
-        return false;
-    }
-    void *p = own_alloc(c, b);
-    if (!p || lbm3::launch_rest3(c->s, p) != hipSuccess) {  // slots no step writes
-        c->no_pair = true;
-        return false;
-    }
-    c->s.f[1] = p;
-    return true;
+    if (s.aa)
+        s.f[1] = scratch;
+    return s;
 }
 
-int lbm3d_step(lbm3d_ctx *c, int64_t n)
+// DENSE_AA: the lattice a call of n steps can use beside the context's own, in bytes.
+// Steps that are being captured run in place.
+static size_t step_scratch(const lbm3d_ctx *c, int64_t n)
 {
-    LBM3_CHECK_CTX(c);
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const int64_t before = c->cur == 0 ? 1 : 0;
+    if (!c->s.aa || n - before < 4 || !lbm3::pair_supported3(pair_state(c, c->s.f[0])) ||
+        (c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+         st != hipStreamCaptureStatusNone))
+        return 0;
+    return (size_t)Q * stored_nodes(c) * c->pop_bytes;
+}
+
+static int step_impl(lbm3d_ctx *c, int64_t n, void *scratch)
+{
     if (n < 0)
         return fail(c, LBM_ERR_INVALID, "n must be >= 0");
     auto single = [&]() -> int {
@@ -495,21 +485,24 @@ int lbm3d_step(lbm3d_ctx *c, int64_t n)
     };
     // Pairs of steps where the layout has them.  A pair leaves the state of an A-B
     // context in the other lattice, as one step does; the AA layout takes pairs from
-    // an odd number of steps on, into its second lattice (parity kept).
+    // an odd number of steps on (parity kept), there and back between its lattice
+    // and the one lent.
     const bool aa = c->s.aa != 0;
-    if (n >= 2 && ensure_pair_lattice(c)) {
-        if (aa && c->cur == 0)
+    const lbm3::State3 s = pair_state(c, scratch);
+    if (n >= 2 && lbm3::pair_supported3(s)) {
+        if (aa && c->cur == 0 && n >= 5)
             if (int rc = single())
                 return rc;
-        int64_t pairs = n / 2;
-        if (c->recorded && (pairs & 1))
-            --pairs;  // two single steps instead: as many launches as steps, modulo 2
-        for (; pairs > 0; --pairs) {
-            LBM3_HIP(c, lbm3::launch_pair3(c->s, c->cur));
+        int64_t pairs = aa && c->cur == 0 ? 0 : n / 2;
+        if (aa || c->recorded)
+            pairs &= ~int64_t(1);  // two single steps instead: the state ends up in the
+                                   // lattice that single steps leave it in
+        for (int from = c->cur; pairs > 0; --pairs) {
             if (aa)
-                std::swap(c->s.f[0], c->s.f[1]);
-            else
-                c->cur ^= 1;
+                from = (int)(pairs & 1);
+            LBM3_HIP(c, lbm3::launch_pair3(s, from));
+            if (!aa)
+                from = c->cur ^= 1;
             c->t += 2;
             n -= 2;
         }
@@ -518,6 +511,31 @@ int lbm3d_step(lbm3d_ctx *c, int64_t n)
         if (int rc = single())
             return rc;
     return LBM_OK;
+}
+
+int lbm3d_step(lbm3d_ctx *c, int64_t n)
+{
+    LBM3_CHECK_CTX(c);
+    return step_impl(c, n, nullptr);
+}
+
+int lbm3d_step_scratch_bytes(lbm3d_ctx *c, int64_t n, size_t *bytes)
+{
+    LBM3_CHECK_CTX(c);
+    if (!bytes)
+        return fail(c, LBM_ERR_INVALID, "bytes is NULL");
+    *bytes = step_scratch(c, n);
+    return LBM_OK;
+}
+
+int lbm3d_step_scratch(lbm3d_ctx *c, int64_t n, void *scratch, size_t bytes)
+{
+    LBM3_CHECK_CTX(c);
+    const size_t need = scratch ? step_scratch(c, n) : 0;
+    if (bytes < need)
+        return fail(c, LBM_ERR_INVALID,
+                    "the scratch memory is smaller than lbm3d_step_scratch_bytes");
+    return step_impl(c, n, need ? scratch : nullptr);
 }
 
 int lbm3d_macroscopic(lbm3d_ctx *c, double *rho, double *ux, double *uy, double *uz)

@@ -31,8 +31,8 @@ struct DevState {
     int nx = 0, ny = 0;
     int pitch = 0;        // dense: row pitch in elements (multiple of 64)
     size_t plane = 0;     // elements per population plane of one lattice
-    void *f[2] = {nullptr, nullptr};  // lattices (DENSE_AA: f[1] = second lattice of
-                                      // launch_steps, null if there is none)
+    void *f[2] = {nullptr, nullptr};  // lattices (DENSE_AA: f[1] = memory lent for one
+                                      // call, used by launch_steps only; else null)
     const uint8_t *type = nullptr;    // node-type codes (dense / tiled)
     const uint8_t *nmask = nullptr;   // solid-neighbour bits (dense / tiled)
     const uint32_t *seg_interior = nullptr;  // dense: per 256-node row segment, 1 = all interior
@@ -81,17 +81,6 @@ int64_t reduction_capacity(const DevState &s);
 // even or odd kernel).
 hipError_t launch_step(const DevState &s, int64_t t, int cur);
 
-// Whether the AA layout may allocate a second lattice of that many bytes for steps that
-// share a launch: no more than 4 GiB (256^3 in FP64: 890 us per step in place, 534 in
-// pairs), and while at least half of the device's memory is free, so that programs
-// that fill it keep the layout's one lattice.
-inline bool spare_lattice(size_t bytes)
-{
-    size_t free = 0, total = 0;
-    return bytes <= (size_t(4) << 30) && hipMemGetInfo(&free, &total) == hipSuccess &&
-           free >= total / 2;
-}
-
 // Squares of n x n nodes, which lose a ring of nodes per step, that cover the lattice.
 inline int64_t square_blocks(int nx, int ny, int n, int steps)
 {
@@ -128,8 +117,9 @@ inline int square_steps(int nx, int ny, int dtype, int &n)
 // Most steps one launch_steps call takes (1: this lattice runs single steps only).
 int max_fused_steps(const DevState &s);
 // `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in
-// one launch, bitwise those of `steps` launch_step calls.  DENSE_AA: from f[0] to
-// f[1], an even number of steps from an odd time step.
+// one launch, bitwise those of `steps` launch_step calls (fluid nodes; the slots of solid
+// nodes are neither read into a result nor written).  DENSE_AA: an even number of steps
+// from an odd time step, f[1] being lent memory.
 hipError_t launch_steps(const DevState &s, int cur, int steps);
 #define LBM_DECLARE_STEPS(place)                                              \
     hipError_t launch_steps_##place##_f64(const DevState &, int, int);        \

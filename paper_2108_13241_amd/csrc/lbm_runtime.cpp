@@ -78,7 +78,6 @@ struct lbm_ctx {
     hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
     int32_t graph_len = 0;
     hipStream_t capture_stream = nullptr;
-    bool no_pair = false;  // AA: there is no room for a second lattice
     // A call of this context was captured into a caller's graph: from then on every
     // step(n) leaves the state in the buffer that n single steps would, so that
     // the graph finds it there whatever runs between its replays.
@@ -734,27 +733,31 @@ int lbm_set_force(lbm_ctx *c, const double *force)
     return LBM_OK;
 }
 
-// Most steps a launch may take on this context.
-static int fused_limit(const lbm_ctx *c)
+static bool is_capturing(const lbm_ctx *c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+           st != hipStreamCaptureStatusNone;
+}
+
+// The lattices that launch_steps works on: the layout's own two, or DENSE_AA's one and a
+// lattice the caller lends for the call (null: steps in place).
+static lbm::DevState fused_state(const lbm_ctx *c, void *scratch)
 {
     lbm::DevState s = c->s;
-    if (s.layout == LBM_DENSE_AA && !s.f[1]) {
-        // the second lattice is allocated on the first call that uses it
-        if (c->no_pair)
-            return 1;
-        s.f[1] = s.f[0];
-    }
-    return lbm::max_fused_steps(s);
+    if (s.layout == LBM_DENSE_AA)
+        s.f[1] = scratch;
+    return s;
 }
 
 // Graph length for this context: explicit setting, or (auto) 32 steps for
 // lattices small enough that host launch overhead is a visible share of a step
 // and that run one launch per step.
-static int32_t graph_length(const lbm_ctx *c)
+static int32_t graph_length(const lbm_ctx *c, void *scratch)
 {
     if (c->graph_steps >= 0)
         return c->graph_steps;
-    if (fused_limit(c) > 1 && !(c->s.layout == LBM_DENSE_AA && c->recorded))
+    if (lbm::max_fused_steps(fused_state(c, scratch)) > 1)
         return 0;
     const double bytes = 18.0 * (double)c->s.plane * c->pop_bytes;
     return bytes < 128.0 * (1 << 20) ? 32 : 0;
@@ -769,8 +772,6 @@ static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
     hipError_t e = steps > 1 ? lbm::launch_steps(s, c->cur, steps) : lbm::launch_step(s, c->t, c->cur);
     if (c->s.layout != LBM_DENSE_AA)
         c->cur ^= 1;
-    else if (steps > 1)
-        std::swap(c->s.f[0], c->s.f[1]);
     c->t += steps;
     return e;
 }
@@ -802,38 +803,50 @@ static hipError_t step_groups(lbm_ctx *c, hipStream_t stream, int64_t n, bool ke
     return e;
 }
 
+// Fused launches of the AA layout for a call of n steps: `before` steps in place, then
+// `launches` of an even number of steps each, `m` in all.  An even number of launches, so
+// that the last one ends in the context's lattice.  Small lattices, where a step takes as
+// long as its launch, need eight steps to make up for borrowing (about 10 us).
+struct AaPlan {
+    int64_t before, m, launches;
+};
+
+static AaPlan aa_plan(const lbm_ctx *c, const lbm::DevState &s, int64_t n)
+{
+    AaPlan p{(c->t & 1) ? 0 : 1, 0, 0};
+    const int64_t kmax = lbm::max_fused_steps(s) & ~1, m = (n - p.before) & ~int64_t(1);
+    if (kmax < 2 || m < ((int64_t)s.nx * s.ny < 100000 ? 8 : 4))
+        return p;
+    p.launches = (m + kmax - 1) / kmax;
+    p.launches += p.launches & 1;
+    if (2 * p.launches > m)
+        p.launches -= 2;
+    p.m = std::min(m, p.launches * kmax);
+    return p;
+}
+
 // Launch n steps of the AA layout.  After an odd number of steps its lattice is
 // an A-B lattice with opposite slots exchanged, which the fused kernel advances
-// by an even number of steps into the second lattice; a single in-place step
-// before it (from an even time step) and one after it (to an even one) do the
-// rest.
-static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, bool in_place)
+// by an even number of steps into the other lattice: with one lent by the caller
+// the launches go there and back.  A single in-place step before them (from an even
+// time step) and some after them do the rest.
+static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, void *scratch)
 {
     hipError_t e = hipSuccess;
-    const int64_t before = (c->t & 1) ? 0 : 1;
-    if (!in_place && n - before >= 2 && fused_limit(c) > 1) {
-        if (!c->s.f[1]) {
-            const size_t b = (size_t)9 * c->s.plane * c->pop_bytes;
-            c->s.f[1] = lbm::spare_lattice(b) ? own_alloc(c, b) : nullptr;
-            c->no_pair = c->s.f[1] == nullptr;
-            if (c->s.f[1]) {
-                lbm::DevState s = c->s;
-                s.stream = stream;
-                e = lbm::launch_rest(s, c->s.f[1]);  // slots no step writes (solid nodes)
-            }
+    lbm::DevState s = fused_state(c, scratch);
+    s.stream = stream;
+    const AaPlan p = aa_plan(c, s, n);
+    if (p.launches) {
+        if (p.before)
+            e = step_group(c, stream, 1);
+        int64_t m = p.m;
+        for (int64_t l = p.launches; l > 0 && e == hipSuccess; --l) {
+            const int64_t steps = 2 * ((m + 2 * l - 1) / (2 * l));  // equal parts
+            e = lbm::launch_steps(s, (int)(l & 1), (int)steps);
+            c->t += steps;
+            m -= steps;
         }
-        if (c->s.f[1]) {
-            if (before && e == hipSuccess) {
-                e = step_group(c, stream, 1);
-                --n;
-            }
-            const int64_t kmax = lbm::max_fused_steps(c->s) & ~1;
-            while (n >= 2 && e == hipSuccess) {
-                const int64_t steps = std::min(n & ~int64_t(1), kmax);
-                e = step_group(c, stream, (int)steps);
-                n -= steps;
-            }
-        }
+        n -= p.before + p.m;
     }
     for (; n > 0 && e == hipSuccess; --n)
         e = step_group(c, stream, 1);
@@ -852,7 +865,7 @@ static int capture_graph(lbm_ctx *c, int key, int32_t G)
     LBM_HIP(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
     // G is even and so is the number of launches: a replay returns to the parity
     // it started from
-    hipError_t e = c->s.layout == LBM_DENSE_AA ? step_aa(c, c->capture_stream, G, true)
+    hipError_t e = c->s.layout == LBM_DENSE_AA ? step_aa(c, c->capture_stream, G, nullptr)
                                                : step_groups(c, c->capture_stream, G, true);
     hipError_t e2 = hipStreamEndCapture(c->capture_stream, &graph);
     c->t = t0;
@@ -879,12 +892,21 @@ int lbm_set_graph_steps(lbm_ctx *c, int32_t steps)
     return LBM_OK;
 }
 
-int lbm_step(lbm_ctx *c, int64_t n)
+// DENSE_AA: the lattice a call of n steps can use beside the context's own, in bytes.
+// Steps recorded into a graph, the caller's or the context's own, run in place.
+static size_t step_scratch(const lbm_ctx *c, int64_t n)
 {
-    LBM_CHECK_CTX(c);
+    if (c->s.layout != LBM_DENSE_AA || n < 4 || c->graph_steps > 0 ||
+        !aa_plan(c, fused_state(c, c->s.f[0]), n).launches || is_capturing(c))
+        return 0;
+    return (size_t)9 * c->s.plane * c->pop_bytes;
+}
+
+static int step_impl(lbm_ctx *c, int64_t n, void *scratch)
+{
     if (n < 0)
         return fail(c, LBM_ERR_INVALID, "n must be >= 0");
-    const int32_t G = graph_length(c);
+    const int32_t G = graph_length(c, scratch);
     if (G >= 2 && c->graph_len != 0 && c->graph_len != G)
         drop_graphs(c);
     while (G >= 2 && n >= G) {
@@ -901,15 +923,39 @@ int lbm_step(lbm_ctx *c, int64_t n)
     }
     if (n == 0)
         return LBM_OK;
-    // Where a graph holds this context's buffers, each call ends in the buffer
-    // that single steps would end in: the AA layout steps in place, the others keep
-    // the parity of the lattice that holds the state (their own graphs, one per
-    // lattice, need no such care).
+    // Where a caller's graph holds this context's buffers, each call ends in the buffer
+    // that single steps would end in: the two-lattice layouts keep the parity of the
+    // lattice that holds the state (their own graphs, one per lattice, need no such
+    // care); the AA layout's state never leaves its lattice.
     if (c->s.layout == LBM_DENSE_AA)
-        LBM_HIP(c, step_aa(c, c->s.stream, n, c->recorded || c->graph_len != 0));
+        LBM_HIP(c, step_aa(c, c->s.stream, n, scratch));
     else
         LBM_HIP(c, step_groups(c, c->s.stream, n, c->recorded));
     return LBM_OK;
+}
+
+int lbm_step(lbm_ctx *c, int64_t n)
+{
+    LBM_CHECK_CTX(c);
+    return step_impl(c, n, nullptr);
+}
+
+int lbm_step_scratch_bytes(lbm_ctx *c, int64_t n, size_t *bytes)
+{
+    LBM_CHECK_CTX(c);
+    if (!bytes)
+        return fail(c, LBM_ERR_INVALID, "bytes is NULL");
+    *bytes = step_scratch(c, n);
+    return LBM_OK;
+}
+
+int lbm_step_scratch(lbm_ctx *c, int64_t n, void *scratch, size_t bytes)
+{
+    LBM_CHECK_CTX(c);
+    const size_t need = scratch ? step_scratch(c, n) : 0;
+    if (bytes < need)
+        return fail(c, LBM_ERR_INVALID, "the scratch memory is smaller than lbm_step_scratch_bytes");
+    return step_impl(c, n, need ? scratch : nullptr);
 }
 
 int lbm_macroscopic_device(lbm_ctx *c, void *rho, void *ux, void *uy)
