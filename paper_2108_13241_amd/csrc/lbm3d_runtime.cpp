@@ -104,7 +104,11 @@ void *raw_alloc(const lbm3d_ctx *c, size_t bytes)
     if (c->alloc)
         return c->alloc(bytes, c->user);
     void *p = nullptr;
-    return hipMalloc(&p, bytes) == hipSuccess ? p : nullptr;
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();  // or the next launch would report it
+        return nullptr;
+    }
+    return p;
 }
 
 void raw_free(const lbm3d_ctx *c, void *p)

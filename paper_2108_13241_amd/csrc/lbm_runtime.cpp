@@ -136,8 +136,10 @@ void *raw_alloc(const Allocator &a, size_t bytes)
     if (a.alloc)
         return a.alloc(bytes, a.user);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess)
+    if (hipMalloc(&p, bytes) != hipSuccess) {
+        (void)hipGetLastError();  // or the next launch would report it
         return nullptr;
+    }
     return p;
 }
 
