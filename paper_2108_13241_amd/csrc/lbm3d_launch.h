@@ -69,8 +69,9 @@ hipError_t launch_step3(const State3 &s, int cur);
 // Two steps in one launch, from lattice `from` to 1 - from (DENSE_AA: after an odd number
 // of steps, f[1] being lent memory), bitwise those of two launch_step3 calls (fluid
 // nodes; the slots of solid nodes are neither read into a result nor written).
-// pair_supported3: whether the lattice has such a launch (dense layouts with two
-// lattices, halfway rule) and it is faster than two.
+// pair_compiled3: whether there is a kernel for the lattice; launch_pair3 fails without.
+// pair_supported3: and it is faster than two launches.
+bool pair_compiled3(const State3 &s);
 bool pair_supported3(const State3 &s);
 hipError_t launch_pair3(const State3 &s, int from);
 // Equilibrium of device FP64 [nz][ny][nx] fields (NULL: rho = 1, u = 0) into the

@@ -253,6 +253,8 @@ inline int pair_planes(int nz, uint32_t tiles)
     return best;
 }
 
+inline bool forced(const State3 &s) { return s.gx != 0.0 || s.gy != 0.0 || s.gz != 0.0; }
+
 template <class ST, bool FORCE, bool TRT, bool MRT, bool WALLS, bool OPP>
 void pair_launch(const State3 &s, const void *src, void *dst)
 {
@@ -280,6 +282,7 @@ void pair_launch(const State3 &s, const void *src, void *dst)
         Rates3<R>{(R)s.omega_m, (R)s.s_e, (R)s.s_eps, (R)s.s_q, (R)s.s_pi, (R)s.s_m});
 }
 
+// pair_compiled3 has excluded what is not compiled here.
 template <class ST, bool TRT, bool MRT, bool OPP>
 void pair_phys(const State3 &s, const void *src, void *dst)
 {
@@ -288,7 +291,7 @@ void pair_phys(const State3 &s, const void *src, void *dst)
     } else {
         // (MRT with a force: FP64 only)
         constexpr bool kForce = !MRT || sizeof(typename ST::mem) == 8;
-        if (kForce && (s.gx != 0.0 || s.gy != 0.0 || s.gz != 0.0))
+        if (kForce && forced(s))
             pair_launch<ST, kForce, TRT, MRT, true, OPP>(s, src, dst);
         else if (s.interior_frac == 1.0)
             pair_launch<ST, false, TRT, MRT, false, OPP>(s, src, dst);
@@ -318,6 +321,19 @@ hipError_t pair_typed(const State3 &s, const void *src, void *dst)
 
 }  // namespace
 
+// The lattices that k_pair3 is compiled for: dense ones under the halfway rule, with the node
+// offsets inside a z plane in 32 bits; 16-bit types without solid nodes and force, FP32
+// MRT without a force (both slower than single steps otherwise, see below).
+bool pair_compiled3(const State3 &s)
+{
+    if (s.list || s.blocks || s.fullway || !s.f[1] ||
+        (uint64_t)s.ny * (uint32_t)s.pitch * Q >= (uint64_t(1) << 31))
+        return false;
+    if (s.dtype == LBM_F16_SHIFTED || s.dtype == LBM_BF16_SHIFTED)
+        return s.interior_frac == 1.0 && !forced(s);
+    return !(s.dtype == LBM_F32 && s.mrt && forced(s));
+}
+
 // The 32-bit and 64-bit types take pairs from the size on at which a pair beats two
 // launches.  Measured, us per step, single against pairs: 32^3 FP32 4.9 / 4.8, with
 // a force 4.1 / 6.4; 48^3 6.6 / 5.0 and 7.1 / 6.7.  Where most rows hold solid nodes
@@ -329,15 +345,11 @@ hipError_t pair_typed(const State3 &s, const void *src, void *dst)
 // a force in FP32 needs more registers than 16 wavefronts have (192^3 281 / 310).
 bool pair_supported3(const State3 &s)
 {
-    const uint64_t plane = (uint64_t)s.ny * (uint32_t)s.pitch, nodes = plane * (uint32_t)s.nz;
-    // a node's offset inside a z plane is 32-bit
-    if (s.list || s.blocks || s.fullway || !s.f[1] || plane * Q >= (uint64_t(1) << 31))
+    if (!pair_compiled3(s))
         return false;
-    const bool force = s.gx != 0.0 || s.gy != 0.0 || s.gz != 0.0;
+    const uint64_t nodes = (uint64_t)s.ny * (uint32_t)s.pitch * (uint32_t)s.nz;
     if (s.dtype == LBM_F16_SHIFTED || s.dtype == LBM_BF16_SHIFTED)
-        return s.interior_frac == 1.0 && !force && nodes * Q * 2 > (uint64_t(256) << 20);
-    if (s.dtype == LBM_F32 && s.mrt && force)
-        return false;
+        return nodes * Q * 2 > (uint64_t(256) << 20);
     if (s.interior_frac >= 0.9)
         return nodes >= (1u << 17);
     return nodes >= (s.aa ? 1u << 19 : 1u << 18);
@@ -345,7 +357,7 @@ bool pair_supported3(const State3 &s)
 
 hipError_t launch_pair3(const State3 &s, int from)
 {
-    if (!pair_supported3(s))
+    if (!pair_compiled3(s))
         return hipErrorInvalidValue;
     const void *src = s.f[from];
     void *dst = s.f[1 - from];

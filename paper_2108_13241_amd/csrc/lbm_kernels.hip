@@ -10,6 +10,8 @@
 // Offsets inside one lattice are 32-bit element indices (the runtime checks
 // 9 * nodes < 2^32).  The indirect layout's neighbours use the compact
 // row-rank description of lbm_plan.h (6 bytes per node).
+#include <algorithm>
+
 #include "lbm_dense.h"
 #include "lbm_device.h"
 #include "lbm_launch.h"
@@ -1547,18 +1549,16 @@ int max_fused_steps(const DevState &s)
         return 1;
     if (k)
         return k;
-    // StepsShape::kMax
     const bool force = s.gx != 0.0 || s.gy != 0.0;
     const bool sparse = s.layout == kTiled16 || s.layout == kIndirect;
-    return s.mrt || s.open || s.alpha || (s.trt && force) ||
-                   (sparse && (s.dtype == kF64 || s.trt || force))
-               ? 6
-               : 8;
+    return std::max(1, strip_steps(s.dtype == kF64, s.dtype > kF32, sparse, force && !s.alpha,
+                                   s.alpha != nullptr, s.open != 0, s.trt != 0, s.mrt != 0));
 }
 
 hipError_t launch_steps(const DevState &s, int cur, int steps)
 {
-    if (steps < 2 || steps > max_fused_steps(s) || (s.layout == kDenseAA && steps % 2 != 0))
+    // the number of steps is checked by the variant's launch
+    if (s.fullway || !s.f[1] || s.fluid_frac == 0.0 || (s.layout == kDenseAA && steps % 2 != 0))
         return hipErrorInvalidValue;
     typedef hipError_t (*launch)(const DevState &, int, int);
     static const launch table[4][4] = {

@@ -114,7 +114,28 @@ inline int square_steps(int nx, int ny, int dtype, int &n)
     return 0;
 }
 
-// Most steps one launch_steps call takes (1: this lattice runs single steps only).
+// The strip kernels of the fused steps that are compiled: the most steps a launch of one may
+// take (its block size and registers), 0 for a variant that there is none of.  Eight steps
+// in flight where the registers allow two workgroups of 8 S wavefronts per CU; the
+// variants with more live values (MRT, drag, open boundaries, TRT with a force, most on
+// sparse layouts) take six.  MRT costs the 16-bit types more than strips save: sparse
+// layouts, and dense ones with a force or drag or open boundaries, take it on squares only.
+constexpr bool strip_heavy(bool f64, bool sparse, bool force, bool drag, bool open, bool trt,
+                           bool mrt)
+{
+    const bool forced = force || drag;
+    return mrt || open || drag || (trt && forced) || (sparse && (f64 || trt || forced));
+}
+constexpr int strip_steps(bool f64, bool bits16, bool sparse, bool force, bool drag, bool open,
+                          bool trt, bool mrt)
+{
+    if (bits16 && mrt && (sparse || force || drag || open))
+        return 0;
+    return strip_heavy(f64, sparse, force, drag, open, trt, mrt) ? 6 : 8;
+}
+
+// Most steps one launch_steps call takes where that is faster than single steps (1: this
+// lattice runs single steps only).
 int max_fused_steps(const DevState &s);
 // `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in
 // one launch, bitwise those of `steps` launch_step calls (fluid nodes; the slots of solid

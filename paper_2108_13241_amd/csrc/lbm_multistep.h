@@ -560,25 +560,24 @@ __global__ __launch_bounds__(N *N) void k_steps_square(const DenseArgs<ST> k, co
 
 // ---------------------------------------------------------------- dispatch --
 
-// Shapes of k_steps.  Eight steps in flight where the registers allow two
-// workgroups of 8 S wavefronts per CU (128 VGPRs in FP64 with S = 1, 64 otherwise
-// with S = 2); the variants with more live values (MRT, drag, open boundaries)
-// take six, whose budgets are 168 and 84 (at eight they spill: FP32 MRT 71 us per
-// step against 65 at 4096^2, FP64 with drag 169 against 130).  Six FP64 steps use
-// S = 2, since a workgroup whose wavefronts are no multiple of four loads the
-// SIMDs unevenly (FP64, six steps, S = 1: 190 us per step against 118).
+// Shapes of k_steps: the steps of strip_steps, in 128 VGPRs a lane for eight FP64 steps with
+// S = 1, 64 otherwise with S = 2; the heavy variants' budgets at six are 168 and 84 (at
+// eight they spill: FP32 MRT 71 us per step against 65 at 4096^2, FP64 with drag 169 against
+// 130).  Six FP64 steps use S = 2, since a workgroup whose wavefronts are no multiple of
+// four loads the SIMDs unevenly (FP64, six steps, S = 1: 190 us per step against 118).
 template <class ST, int PH, int PLACE>
 struct StepsShape {
-    static constexpr bool kHeavy =
-        (PH & (kMRT | kOpenBC)) != 0 || (PH & 3) == kDragged ||
-        ((PH & kTRT) != 0 && (PH & 3) != kBGK) ||
-        (PLACE >= kList &&
-         (sizeof(typename ST::mem) == 8 || (PH & kTRT) != 0 || (PH & 3) != kBGK));
-    static constexpr bool kFull = (PH & kMRT) != 0 && (PH & 3) != kBGK &&
-                                  ((PH & kOpenBC) != 0 || PLACE >= kList);
     static constexpr bool kF64 = sizeof(typename ST::mem) == 8;
+    static constexpr bool k16 = sizeof(typename ST::mem) == 2;
+    static constexpr bool kSparse = PLACE >= kList;
+    static constexpr bool kForce = (PH & 3) == kForced, kDrag = (PH & 3) == kDragged;
+    static constexpr bool kOpens = (PH & kOpenBC) != 0;
+    static constexpr bool kTwo = (PH & kTRT) != 0, kMulti = (PH & kMRT) != 0;
+    static constexpr bool kHeavy = strip_heavy(kF64, kSparse, kForce, kDrag, kOpens, kTwo, kMulti);
+    static constexpr bool kFull = kMulti && (kForce || kDrag) && (kOpens || kSparse);
     static constexpr int S = kF64 && !kHeavy ? 1 : 2;
-    static constexpr int kMax = kHeavy ? 6 : 8;
+    static constexpr int kMax =
+        strip_steps(kF64, k16, kSparse, kForce, kDrag, kOpens, kTwo, kMulti);
     static constexpr int kWaves =  // per SIMD
         kF64 ? (kHeavy ? 3 : 4) : (kFull ? 3 : (kHeavy ? 6 : 8));
 };
@@ -612,8 +611,9 @@ inline int strip_rows(int ny, uint32_t nstrips, int K, int per_cu)
     return best_rows;
 }
 
+// Fails, with nothing launched, on a number of steps or a variant that no kernel is made for.
 template <class ST, int PH, bool WALLS, int PLACE>
-void steps_launch(const DevState &s, int cur, int K)
+hipError_t steps_launch(const DevState &s, int cur, int K)
 {
     using M = typename ST::mem;
     using R = typename ST::real;
@@ -647,7 +647,9 @@ void steps_launch(const DevState &s, int cur, int K)
     g.steps = K;
     g.every = s.every;
     int square = 0;
-    square_steps(s.nx, s.ny, s.dtype, square);
+    const int most = square_steps(s.nx, s.ny, s.dtype, square);
+    if (K < 2 || K > (square ? most : Sh::kMax) || (s.every && !square))
+        return hipErrorInvalidValue;
     if (square) {
         const int in = square - 2 * K;
         g.nstrips = (uint32_t)((s.nx + in - 1) / in);
@@ -656,13 +658,9 @@ void steps_launch(const DevState &s, int cur, int K)
             k_steps_square<ST, PH, PLACE, 16><<<blocks, 256, 0, s.stream>>>(k, g);
         else
             k_steps_square<ST, PH, PLACE, 32><<<blocks, 1024, 0, s.stream>>>(k, g);
-        return;
+        return hipGetLastError();
     }
-    // MRT costs the 16-bit types more than its strips save (max_fused_steps): sparse
-    // layouts, and dense ones with a force, take them on squares only
-    constexpr bool kStrips = sizeof(M) > 2 || (PH & kMRT) == 0 ||
-                             (PLACE < kList && (PH & 3) == kBGK);
-    if constexpr (kStrips) {
+    if constexpr (Sh::kMax > 0) {
         g.halo = K <= 4 ? 4 : 8;  // strips start at a multiple of 32 or 64 bytes (FP64)
         const int out = L::kWid - 2 * g.halo;
         g.nstrips = (uint32_t)((s.nx + out - 1) / out);
@@ -674,44 +672,39 @@ void steps_launch(const DevState &s, int cur, int K)
         k_steps<ST, PH, WALLS, PLACE, S, Sh::kMax, Sh::kWaves>
             <<<blocks, (uint32_t)(64 * S * K), lds, s.stream>>>(k, g);
     }
+    return hipGetLastError();
 }
 
 template <class ST, int COLL, int PLACE>
-void steps_phys(const DevState &s, int cur, int K)
+hipError_t steps_phys(const DevState &s, int cur, int K)
 {
     const bool force = s.gx != 0.0 || s.gy != 0.0;
     if (s.open) {
         if (s.alpha)
-            steps_launch<ST, kDragged | kOpenBC | COLL, true, PLACE>(s, cur, K);
-        else if (force)
-            steps_launch<ST, kForced | kOpenBC | COLL, true, PLACE>(s, cur, K);
-        else
-            steps_launch<ST, kBGK | kOpenBC | COLL, true, PLACE>(s, cur, K);
-    } else if (s.alpha) {
-        steps_launch<ST, kDragged | COLL, true, PLACE>(s, cur, K);
-    } else if (force) {
-        steps_launch<ST, kForced | COLL, true, PLACE>(s, cur, K);
-    } else {
-        if constexpr (PLACE < kList) {
-            if (s.interior_frac == 1.0) {
-                steps_launch<ST, kBGK | COLL, false, PLACE>(s, cur, K);
-                return;
-            }
-        }
-        steps_launch<ST, kBGK | COLL, true, PLACE>(s, cur, K);
+            return steps_launch<ST, kDragged | kOpenBC | COLL, true, PLACE>(s, cur, K);
+        if (force)
+            return steps_launch<ST, kForced | kOpenBC | COLL, true, PLACE>(s, cur, K);
+        return steps_launch<ST, kBGK | kOpenBC | COLL, true, PLACE>(s, cur, K);
     }
+    if (s.alpha)
+        return steps_launch<ST, kDragged | COLL, true, PLACE>(s, cur, K);
+    if (force)
+        return steps_launch<ST, kForced | COLL, true, PLACE>(s, cur, K);
+    if constexpr (PLACE < kList) {
+        if (s.interior_frac == 1.0)
+            return steps_launch<ST, kBGK | COLL, false, PLACE>(s, cur, K);
+    }
+    return steps_launch<ST, kBGK | COLL, true, PLACE>(s, cur, K);
 }
 
 template <class ST, int PLACE>
 hipError_t steps_placed(const DevState &s, int cur, int K)
 {
     if (s.mrt)
-        steps_phys<ST, kMRT, PLACE>(s, cur, K);
-    else if (s.trt)
-        steps_phys<ST, kTRT, PLACE>(s, cur, K);
-    else
-        steps_phys<ST, 0, PLACE>(s, cur, K);
-    return hipGetLastError();
+        return steps_phys<ST, kMRT, PLACE>(s, cur, K);
+    if (s.trt)
+        return steps_phys<ST, kTRT, PLACE>(s, cur, K);
+    return steps_phys<ST, 0, PLACE>(s, cur, K);
 }
 
 }  // namespace
