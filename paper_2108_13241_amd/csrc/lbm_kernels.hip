@@ -1503,34 +1503,63 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
 //   9.8 (0.95), 2048^2 34 / 45 and 44 / 45 (0.8); 16 bits 400^2 3.8 / 2.9, 640^2 3.9 / 4.3,
 //   896^2 7.0 / 7.8 (0.8), 1200^2 12.1 / 13.0 (0.8), 14.4 / 13.0 (0.95), 3008^2 47 / 48 and 61 /
 //   60 (0.8), 4096^2 140 / 104 (0.9), MRT 1200^2 13.1 / 18.2 (0.8).
-//   TILED16 is alike.
+//   TILED16 is alike.  MRT with a force in FP64, six steps: INDIRECT 704 x 688 6.6 / 9.6
+//   (0.4) and 12.4 / 9.5 (0.7), 1504^2 26.6 / 28.7 (0.4) and 42.8 / 28.7 (0.7).
 //   Dense, 16 bits: 896^2 with a force 7.2 / 8.5, 640^2 5.4 / 4.5; MRT and force 2048^2 32 /
 //   39, MRT 1200^2 11.0 / 12.2 (AA); open boundaries 1200^2 10.8 / 15.5 (AA), 14.6 / 15.1.  AA
 //   in FP64 with open boundaries 640^2 9.5 / 10.4.
+// A single step of a dense lattice skips the wavefronts and segments without fluid nodes, and
+// the AA layout's writes one lattice less, so single steps of mostly solid lattices win
+// there too (fluid fraction 0.1 and 0.25, 704 x 688 / 4096^2, with a force, six or eight steps):
+//   A-B: FP64 6.1 / 7.4 and 8.8 / 7.5, 137 / 148 and 212 / 149, MRT 6.8 / 9.0, 160 / 184; FP32
+//   4.9 / 4.5, 87 / 81, MRT 5.3 / 6.6, 6.7 / 6.8 (0.4), 92 / 107, 157 / 107 (0.4); FP16 1504^2 13.3 /
+//   14.7 and 19.5 / 14.6.
+//   AA: FP64 6.0 / 7.4 and 7.9 / 7.5, 112 / 148 and 187 / 149, MRT 9.8 / 9.1 (0.4); FP32 4.3 / 4.5 and
+//   5.3 / 4.5, 60 / 81 and 125 / 81, MRT 6.4 / 6.8 (0.4), 7.2 / 6.9 (0.7); FP16 1504^2 13.3 / 14.6
+//   (0.25), 15.4 / 14.7 (0.4), 4096^2 64 / 85 and 86 / 85.
+static bool heavy_collision(const DevState &s)
+{
+    const bool force = s.gx != 0.0 || s.gy != 0.0, drag = s.alpha != nullptr;
+    return strip_heavy(s.dtype == kF64, false, force && !drag, drag, s.open, s.trt, s.mrt);
+}
+
 static bool fused_pays(const DevState &s, int k, int64_t blocks)
 {
     constexpr double kNever = 2.0;
     const bool list = s.layout == kIndirect, sparse = list || s.layout == kTiled16;
+    const bool aa = s.layout == kDenseAA;
     const bool f64 = s.dtype == kF64, f32 = s.dtype == kF32;
     const bool few = k && blocks <= 512, force = s.gx != 0.0 || s.gy != 0.0;
     const int64_t nodes = (int64_t)s.nx * s.ny;
+    double least;  // fluid fraction
     if (sparse) {
-        double least;  // fluid fraction
         if (f64)
-            least = few ? 0.0 : nodes < 700000 ? 0.5 : list ? 0.32 : 0.34;
+            least = few ? 0.0
+                        : s.mrt ? (nodes < 700000 ? 0.58 : 0.46)
+                                : nodes < 700000 ? 0.5 : list ? 0.35 : 0.34;
         else if (f32)
             least = s.mrt ? (few ? 0.6 : 0.85) : few ? 0.0 : k ? 0.65 : 0.45;
         else
             least = s.mrt ? kNever : few ? 0.0 : k ? kNever : nodes < 4000000 ? 0.9 : 0.75;
-        return s.fluid_frac >= least;
+    } else {
+        const bool heavy = heavy_collision(s);
+        if (f64) {
+            if (aa && s.open && !k && nodes < 700000)
+                return false;
+            least = aa ? (heavy ? 0.38 : 0.22) : heavy ? 0.25 : 0.19;
+        } else if (f32) {
+            least = aa ? (heavy ? 0.45 : 0.22) : !heavy ? 0.08 : nodes < 1000000 ? 0.4 : 0.22;
+        } else if (few) {
+            least = 0.0;
+        } else if (s.mrt) {
+            least = !force && !s.alpha && nodes >= 6000000 ? 0.4 : kNever;
+        } else {
+            if (!(k ? blocks <= 800 : !s.open || nodes >= 4000000))
+                return false;
+            least = aa ? (nodes < 6000000 ? 0.36 : 0.25) : 0.16;
+        }
     }
-    if (f64)
-        return !(s.layout == kDenseAA && s.open && !k && nodes < 700000);
-    if (f32 || few)
-        return true;
-    if (s.mrt)
-        return !force && !s.alpha && nodes >= 6000000;
-    return k ? blocks <= 800 : !s.open || nodes >= 4000000;
+    return s.fluid_frac >= least;
 }
 
 int max_fused_steps(const DevState &s)

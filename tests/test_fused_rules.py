@@ -35,6 +35,16 @@ static DevState state(int nx, int ny, int dtype, int layout, int force, int alph
 }
 int main(int argc, char **argv)
 {
+    // lines of "nx ny dtype layout force drag open collision fluid": the steps a launch takes
+    if (argc > 1) {
+        int v[8];
+        double fluid;
+        while (scanf("%d%d%d%d%d%d%d%d%lf", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7,
+                     &fluid) == 9)
+            printf("%d\n", max_fused_steps(state(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7],
+                                                 fluid)));
+        return 0;
+    }
     int bad = 0, seen = 0, fused = 0;
     auto check = [&](bool ok, const DevState &s, const char *what) {
         if (!ok && bad++ < 20)
@@ -113,3 +123,38 @@ def test_rules_name_compiled_launches(driver):
     assert r.returncode == 0, r.stdout + r.stderr
     seen, fused, _, _ = map(int, r.stdout.split("\n")[-2].split())
     assert seen > 5000 and fused > seen // 4
+
+
+F64, F32, F16 = 0, 1, 2
+AB, AA, TILED, LIST = 0, 1, 2, 3
+# (nx, ny, type, layout, force, drag, open, collision (1 TRT, 2 MRT), fluid fraction), whether
+# fused launches were the faster side, by 5 % or more, of discs with a force
+MEASURED = [
+    ((704, 688, F64, AB, 1, 0, 0, 0, 0.1), False), ((704, 688, F64, AB, 1, 0, 0, 0, 0.25), True),
+    ((704, 688, F64, AB, 1, 0, 0, 2, 0.1), False), ((704, 688, F64, AB, 1, 0, 0, 2, 0.4), True),
+    ((4096, 4096, F64, AB, 1, 0, 0, 2, 0.1), False), ((4096, 4096, F64, AB, 1, 0, 0, 0, 0.25), True),
+    ((704, 688, F32, AB, 1, 0, 0, 0, 0.1), True), ((704, 688, F32, AB, 1, 0, 0, 2, 0.1), False),
+    ((1504, 1504, F32, AB, 1, 0, 0, 2, 0.1), False), ((1504, 1504, F32, AB, 1, 0, 0, 2, 0.4), True),
+    ((1504, 1504, F16, AB, 1, 0, 0, 0, 0.1), False), ((1504, 1504, F16, AB, 1, 0, 0, 0, 0.25), True),
+    ((704, 688, F64, AA, 1, 0, 0, 0, 0.1), False), ((4096, 4096, F64, AA, 1, 0, 0, 0, 0.1), False),
+    ((4096, 4096, F64, AA, 1, 0, 0, 0, 0.25), True), ((4096, 4096, F64, AA, 1, 0, 0, 2, 0.1), False),
+    ((4096, 4096, F64, AA, 1, 0, 0, 2, 0.4), True), ((4096, 4096, F32, AA, 1, 0, 0, 0, 0.1), False),
+    ((4096, 4096, F32, AA, 1, 0, 0, 0, 0.25), True), ((4096, 4096, F32, AA, 1, 0, 0, 2, 0.1), False),
+    ((1504, 1504, F32, AA, 1, 0, 0, 2, 0.7), True), ((1504, 1504, F16, AA, 1, 0, 0, 0, 0.25), False),
+    ((4096, 4096, F16, AA, 1, 0, 0, 0, 0.1), False), ((4096, 4096, F16, AA, 1, 0, 0, 0, 0.4), True),
+    ((704, 688, F64, LIST, 1, 0, 0, 2, 0.55), False), ((704, 688, F64, LIST, 1, 0, 0, 2, 0.7), True),
+    ((1504, 1504, F64, LIST, 1, 0, 0, 2, 0.4), False), ((1504, 1504, F64, LIST, 1, 0, 0, 0, 0.4), True),
+    ((4096, 4096, F64, TILED, 1, 0, 0, 0, 0.25), False), ((4096, 4096, F64, TILED, 1, 0, 0, 0, 0.4), True),
+]
+
+
+def _ask(driver, cases):
+    text = "\n".join(" ".join(map(str, c)) for c in cases)
+    r = subprocess.run([driver, "ask"], input=text, capture_output=True, text=True, check=True)
+    return [list(map(int, line.split())) for line in r.stdout.split("\n") if line]
+
+
+def test_faster_side_is_taken(driver):
+    got = _ask(driver, [c for c, _ in MEASURED])
+    wrong = [(c, steps) for (c, fused), (steps, *_) in zip(MEASURED, got) if (steps > 1) != fused]
+    assert not wrong
