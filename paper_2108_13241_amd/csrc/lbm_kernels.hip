@@ -1584,6 +1584,70 @@ int max_fused_steps(const DevState &s)
                                    s.alpha != nullptr, s.open != 0, s.trt != 0, s.mrt != 0));
 }
 
+// Whether the FP64 strips run a number of steps that is no multiple of four on one wavefront
+// each, which loads the SIMDs unevenly (StepsShape; with walls, fluid fraction 0.25, 4096^2:
+// four steps 0.65 of single ones, eight 0.70, five 0.98, six 0.91).
+static bool uneven_fours(const DevState &s)
+{
+    int n = 0;
+    return s.dtype == kF64 && (s.layout == kDenseAB || s.layout == kDenseAA) &&
+           !heavy_collision(s) && s.fluid_frac < 0.4 && !square_steps(s.nx, s.ny, s.dtype, n);
+}
+
+// Fewest steps of a launch that is faster than as many single ones.  A launch of two or three
+// reads and writes as much as one of six and fills the chip worse.  Measured, two / three
+// steps a launch over single steps: TILED16 4096^2 FP32 with walls 1.55 / 0.97, FP64 1.27 /
+// 0.82, fluid fraction 0.4 FP64 1.35 / 1.12, squares FP32 992 x 704 1.10 / 0.99, 704 x 688 1.55 /
+// 1.16 (0.7); INDIRECT 4096^2 0.7 FP64 0.84 / 0.71, FP32 1.00 / 0.67, FP32 MRT 1.17 / 0.98, FP64 0.4
+// 1.05 / 1.13, FP32 0.55 1.11 / 0.75, 704 x 688 1.28 / 1.03; dense 4096^2 FP16 with walls and a
+// force 1.10 / 0.87, FP64 0.25 0.94 / 0.74, FP32 0.1 1.15 / 0.94, MRT FP32 704 x 688 0.4 1.07 / 0.90,
+// 0.7 0.97 / 0.83.  On squares that fill the chip once two steps take 0.6 to 0.9 of two
+// launches (304 x 208; TILED16 in FP32 1.1).
+static int least_steps(const DevState &s)
+{
+    int n = 0;
+    const int k = square_steps(s.nx, s.ny, s.dtype, n);
+    const bool one_round = k && square_blocks(s.nx, s.ny, n, k) <= 256;
+    const bool f64 = s.dtype == kF64, f32 = s.dtype == kF32;
+    if (s.layout == kTiled16)
+        return one_round || (f64 && s.fluid_frac >= 0.7) ? 3 : 4;
+    if (one_round)
+        return 2;
+    if (s.layout == kIndirect)
+        return s.fluid_frac < 0.7 || (f32 && s.mrt) ? 4 : f64 ? 2 : 3;
+    return (f64 || f32) && s.fluid_frac >= (heavy_collision(s) ? 0.6 : 0.4) ? 2 : 3;
+}
+
+int next_steps(const DevState &s, int64_t left)
+{
+    if (left < 2)
+        return 1;
+    const int most = max_fused_steps(s);
+    if (most == 1 || left >= most)
+        return most;
+    if (left < least_steps(s))
+        return 1;
+    return left > 4 && uneven_fours(s) ? 4 : (int)left;
+}
+
+ThereAndBack there_and_back(const DevState &s, int64_t m)
+{
+    ThereAndBack p;
+    const int64_t most = max_fused_steps(s) & ~1;
+    if (most < 2 || m < 2)
+        return p;
+    p.unit = uneven_fours(s) ? 4 : 2;
+    const int64_t least = least_steps(s);
+    int64_t l = (m + most - 1) / most;
+    l += l & 1;
+    // the shortest of equal parts
+    while (l > 0 && std::min(m, l * most) / (2 * l) * 2 < least)
+        l -= 2;
+    p.launches = l;
+    p.steps = std::min(m, l * most);
+    return p;
+}
+
 hipError_t launch_steps(const DevState &s, int cur, int steps)
 {
     // the number of steps is checked by the variant's launch

@@ -137,6 +137,25 @@ constexpr int strip_steps(bool f64, bool bits16, bool sparse, bool force, bool d
 // Most steps one launch_steps call takes where that is faster than single steps (1: this
 // lattice runs single steps only).
 int max_fused_steps(const DevState &s);
+// Steps of the next launch of a call with `left` steps to go: the most, or the rest where one
+// launch of so few is faster than single steps, or 1.
+int next_steps(const DevState &s, int64_t left);
+// Fused launches that end in the lattice they start from, for `m` steps (even) of the AA
+// layout: an even number of launches, sharing at most m steps in even parts (0: none).
+struct ThereAndBack {
+    int64_t launches = 0, steps = 0;
+    int unit = 2;
+    // Steps of the next launch; updates both counts.
+    int next()
+    {
+        const int64_t even = unit * ((steps + unit * launches - 1) / (unit * launches));
+        const int64_t k = even < steps - 2 * (launches - 1) ? even : steps - 2 * (launches - 1);
+        steps -= k;
+        --launches;
+        return (int)k;
+    }
+};
+ThereAndBack there_and_back(const DevState &s, int64_t m);
 // `steps` (2 .. max_fused_steps) time steps from lattice `cur` to lattice 1 - cur in
 // one launch, bitwise those of `steps` launch_step calls (fluid nodes; the slots of solid
 // nodes are neither read into a result nor written).  DENSE_AA: an even number of steps

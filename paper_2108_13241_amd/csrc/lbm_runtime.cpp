@@ -779,51 +779,48 @@ static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
 }
 
 // Launch n steps of a two-lattice layout: the most a launch takes, as often as they
-// fit, then the rest (a launch of fewer steps costs about what its share of the
+// fit, then the rest (next_steps; a launch of fewer steps costs about what its share of the
 // wavefronts does, so equal parts would gain nothing).  keep_parity: as many
 // launches as n, modulo 2, so that a recorded sequence leaves the state in the
 // lattice that n single steps would.
 static hipError_t step_groups(lbm_ctx *c, hipStream_t stream, int64_t n, bool keep_parity)
 {
-    const int64_t kmax = lbm::max_fused_steps(c->s);
-    hipError_t e = hipSuccess;
-    if (keep_parity && ((((n + kmax - 1) / kmax) ^ n) & 1)) {
-        e = step_group(c, stream, 1);
-        --n;
-        // n steps now, again with launches of n's parity: one more single step
-        // wherever the count would be off
-        if ((((n + kmax - 1) / kmax) ^ n) & 1) {
-            e = e == hipSuccess ? step_group(c, stream, 1) : e;
-            --n;
-        }
+    bool split = false;  // one launch more
+    if (keep_parity) {
+        const int64_t most = lbm::next_steps(c->s, n);
+        int64_t rest = n % most, launches = n / most;
+        for (; rest > 0; ++launches)
+            rest -= lbm::next_steps(c->s, rest);
+        split = (launches ^ n) & 1;
     }
+    hipError_t e = hipSuccess;
     while (n > 0 && e == hipSuccess) {
-        const int64_t steps = std::min(n, kmax);
-        e = step_group(c, stream, (int)steps);
+        const int steps = lbm::next_steps(c->s, n);
+        const int half = split ? steps / 2 : 0;
+        if (half) {
+            e = step_group(c, stream, half);
+            split = false;
+        }
+        e = e == hipSuccess ? step_group(c, stream, steps - half) : e;
         n -= steps;
     }
     return e;
 }
 
-// Fused launches of the AA layout for a call of n steps: `before` steps in place, then
-// `launches` of an even number of steps each, `m` in all.  An even number of launches, so
-// that the last one ends in the context's lattice.  Small lattices, where a step takes as
-// long as its launch, need eight steps to make up for borrowing (about 10 us).
+// A call of n steps of the AA layout: `before` steps in place, then fused launches, the rest
+// in place.  Small lattices, where a step takes as long as its launch, need eight fused
+// steps to make up for borrowing (about 10 us).
 struct AaPlan {
-    int64_t before, m, launches;
+    int64_t before;
+    lbm::ThereAndBack fused;
 };
 
 static AaPlan aa_plan(const lbm_ctx *c, const lbm::DevState &s, int64_t n)
 {
-    AaPlan p{(c->t & 1) ? 0 : 1, 0, 0};
-    const int64_t kmax = lbm::max_fused_steps(s) & ~1, m = (n - p.before) & ~int64_t(1);
-    if (kmax < 2 || m < ((int64_t)s.nx * s.ny < 100000 ? 8 : 4))
-        return p;
-    p.launches = (m + kmax - 1) / kmax;
-    p.launches += p.launches & 1;
-    if (2 * p.launches > m)
-        p.launches -= 2;
-    p.m = std::min(m, p.launches * kmax);
+    AaPlan p{(c->t & 1) ? 0 : 1, {}};
+    const int64_t m = (n - p.before) & ~int64_t(1);
+    if (m >= ((int64_t)s.nx * s.ny < 100000 ? 8 : 4))
+        p.fused = lbm::there_and_back(s, m);
     return p;
 }
 
@@ -837,18 +834,16 @@ static hipError_t step_aa(lbm_ctx *c, hipStream_t stream, int64_t n, void *scrat
     hipError_t e = hipSuccess;
     lbm::DevState s = fused_state(c, scratch);
     s.stream = stream;
-    const AaPlan p = aa_plan(c, s, n);
-    if (p.launches) {
+    AaPlan p = aa_plan(c, s, n);
+    if (p.fused.launches) {
+        n -= p.before + p.fused.steps;
         if (p.before)
             e = step_group(c, stream, 1);
-        int64_t m = p.m;
-        for (int64_t l = p.launches; l > 0 && e == hipSuccess; --l) {
-            const int64_t steps = 2 * ((m + 2 * l - 1) / (2 * l));  // equal parts
-            e = lbm::launch_steps(s, (int)(l & 1), (int)steps);
+        for (int from = 0; p.fused.launches > 0 && e == hipSuccess; from ^= 1) {
+            const int steps = p.fused.next();
+            e = lbm::launch_steps(s, from, steps);
             c->t += steps;
-            m -= steps;
         }
-        n -= p.before + p.m;
     }
     for (; n > 0 && e == hipSuccess; --n)
         e = step_group(c, stream, 1);
@@ -899,7 +894,7 @@ int lbm_set_graph_steps(lbm_ctx *c, int32_t steps)
 static size_t step_scratch(const lbm_ctx *c, int64_t n)
 {
     if (c->s.layout != LBM_DENSE_AA || n < 4 || c->graph_steps > 0 ||
-        !aa_plan(c, fused_state(c, c->s.f[0]), n).launches || is_capturing(c))
+        !aa_plan(c, fused_state(c, c->s.f[0]), n).fused.launches || is_capturing(c))
         return 0;
     return (size_t)9 * c->s.plane * c->pop_bytes;
 }

@@ -35,14 +35,16 @@ static DevState state(int nx, int ny, int dtype, int layout, int force, int alph
 }
 int main(int argc, char **argv)
 {
-    // lines of "nx ny dtype layout force drag open collision fluid": the steps a launch takes
+    // lines of "nx ny dtype layout force drag open collision fluid left": the steps a launch
+    // takes, and those of the next one of a call with `left` steps to go
     if (argc > 1) {
-        int v[8];
+        int v[8], left;
         double fluid;
-        while (scanf("%d%d%d%d%d%d%d%d%lf", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7,
-                     &fluid) == 9)
-            printf("%d\n", max_fused_steps(state(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7],
-                                                 fluid)));
+        while (scanf("%d%d%d%d%d%d%d%d%lf%d", v, v + 1, v + 2, v + 3, v + 4, v + 5, v + 6, v + 7,
+                     &fluid, &left) == 10) {
+            DevState s = state(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], fluid);
+            printf("%d %d\n", max_fused_steps(s), next_steps(s, left));
+        }
         return 0;
     }
     int bad = 0, seen = 0, fused = 0;
@@ -69,6 +71,26 @@ int main(int argc, char **argv)
                                                    s.trt, s.mrt);
         ++seen;
         fused += most > 1;
+        for (int left = 1; left < 70; left += 1 + left / 12) {
+            // every launch of a call is one the kernel takes, and they add up
+            int n = left, launches = 0;
+            for (; n > 0 && launches <= left; ++launches) {
+                const int steps = next_steps(s, n);
+                check(steps == 1 || (steps >= 2 && steps <= most && steps <= n), s, "next steps");
+                n -= steps;
+            }
+            check(n == 0, s, "steps left");
+            ThereAndBack p = there_and_back(s, left & ~1);
+            const int64_t m = p.steps;
+            check(p.launches % 2 == 0 && m % 2 == 0 && m <= left, s, "there and back");
+            int64_t sum = 0;
+            while (p.launches > 0 && sum <= left) {
+                const int steps = p.next();
+                check(steps >= 2 && steps % 2 == 0 && steps <= most, s, "even launch");
+                sum += steps;
+            }
+            check(sum == m && p.steps == 0, s, "even steps");
+        }
         check(most == 1 || (most >= 2 && most <= limit), s, "steps beyond the kernel's");
         // one more than the kernel takes, and any number where there is none
         check(launch_steps(s, 0, (layout == kDenseAA ? limit + 2 - limit % 2 : limit + 1)) ==
@@ -148,6 +170,19 @@ MEASURED = [
 ]
 
 
+# the same with the steps to go, and the steps of the next launch: two or three steps a launch where
+# single steps were faster
+TAILS = [
+    ((4096, 4096, F32, TILED, 1, 0, 0, 0, 0.97, 2), 1), ((4096, 4096, F64, TILED, 1, 0, 0, 0, 0.4, 3), 1),
+    ((704, 688, F32, TILED, 1, 0, 0, 0, 0.7, 10), 4), ((704, 688, F32, TILED, 1, 0, 0, 0, 0.7, 2), 1),
+    ((1504, 1504, F64, LIST, 1, 0, 0, 0, 0.4, 3), 1), ((4096, 4096, F64, LIST, 1, 0, 0, 0, 0.7, 2), 2),
+    ((4096, 4096, F16, AB, 1, 0, 0, 0, 0.97, 2), 1), ((4096, 4096, F64, AB, 1, 0, 0, 0, 0.25, 5), 4),
+    ((4096, 4096, F64, AB, 0, 0, 0, 0, 1.0, 5), 5), ((4096, 4096, F64, AB, 0, 0, 0, 0, 1.0, 2), 2),
+    ((4096, 4096, F32, AB, 1, 0, 0, 0, 0.1, 2), 1), ((256, 64, F32, LIST, 1, 0, 0, 0, 0.97, 2), 2),
+    ((4096, 4096, F32, AB, 1, 0, 0, 0, 0.97, 100), 8),
+]
+
+
 def _ask(driver, cases):
     text = "\n".join(" ".join(map(str, c)) for c in cases)
     r = subprocess.run([driver, "ask"], input=text, capture_output=True, text=True, check=True)
@@ -155,6 +190,11 @@ def _ask(driver, cases):
 
 
 def test_faster_side_is_taken(driver):
-    got = _ask(driver, [c for c, _ in MEASURED])
+    got = _ask(driver, [(*c, 100) for c, _ in MEASURED])
     wrong = [(c, steps) for (c, fused), (steps, *_) in zip(MEASURED, got) if (steps > 1) != fused]
     assert not wrong
+
+
+def test_short_rests_take_the_faster_side(driver):
+    got = _ask(driver, [c for c, _ in TAILS])
+    assert [(c, g[1]) for (c, _), g in zip(TAILS, got)] == TAILS
