@@ -343,6 +343,11 @@ bool pair_compiled3(const State3 &s)
 // nodes and force and once a lattice exceeds the 256 MB memory-side cache (200^3 141 /
 // 119, 320^3 485 / 363; 160^3 61 / 66; walls and a force at 256^3 216 / 254).  MRT with
 // a force in FP32 needs more registers than 16 wavefronts have (192^3 281 / 310).
+// A single step skips rows without fluid nodes, in the cache or on the AA layout at little
+// cost, so mostly solid lattices stay with it (spheres, fluid fraction 0.1 / 0.3 / 0.6): A-B
+// FP32 96 x 80 x 64 11.6 / 16.4, 16.2 / 16.8, 18.2 / 16.9, but 128^3 67 / 42 and 84 / 49; AA FP64
+// 128^3 42 / 67, 69 / 77, 90 / 82; AA FP32 96 x 80 x 64 11.9 / 16.2, 13.9 / 16.5, 14.7 / 16.8, 128^3
+// 28 / 37, 44 / 44, 55 / 48, 256 x 256 x 128 97 / 131, 184 / 162, 240 / 177.
 bool pair_supported3(const State3 &s)
 {
     if (!pair_compiled3(s))
@@ -352,7 +357,12 @@ bool pair_supported3(const State3 &s)
         return nodes * Q * 2 > (uint64_t(256) << 20);
     if (s.interior_frac >= 0.9)
         return nodes >= (1u << 17);
-    return nodes >= (s.aa ? 1u << 19 : 1u << 18);
+    const bool f64 = s.dtype == LBM_F64;
+    if (s.aa)
+        return f64 ? nodes >= (1u << 19) && s.fluid_frac >= 0.45
+                   : nodes >= (1u << 20) && s.fluid_frac >= 0.35;
+    const bool cached = 2 * nodes * Q * (f64 ? 8 : 4) <= (uint64_t(256) << 20);
+    return nodes >= (1u << 18) && (f64 || !cached || s.fluid_frac >= 0.45);
 }
 
 hipError_t launch_pair3(const State3 &s, int from)

@@ -338,6 +338,7 @@ int lbm3d_create(lbm3d_ctx **out, int32_t nx, int32_t ny, int32_t nz, const uint
         s.seg_interior = (const uint32_t *)p;
         s.interior_frac = lbm::plan::interior_fraction(seg);
     }
+    s.fluid_frac = (double)c->n_fluid / ((double)nx * ny * nz);
     const size_t lattice = (size_t)Q * stored_nodes(c) * c->pop_bytes;
     s.aa = layout == LBM_DENSE_AA ? 1 : 0;
     for (int k = 0; k < (s.aa ? 1 : 2); ++k) {

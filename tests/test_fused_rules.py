@@ -37,6 +37,20 @@ int main(int argc, char **argv)
 {
     // lines of "nx ny dtype layout force drag open collision fluid left": the steps a launch
     // takes, and those of the next one of a call with `left` steps to go
+    // "3": nx ny nz dtype aa force fluid, whether pairs of D3Q19 steps are taken
+    if (argc > 1 && !strcmp(argv[1], "3")) {
+        int v[6];
+        double fluid;
+        while (scanf("%d%d%d%d%d%d%lf", v, v + 1, v + 2, v + 3, v + 4, v + 5, &fluid) == 7) {
+            lbm3::State3 s;
+            s.nx = v[0]; s.ny = v[1]; s.nz = v[2]; s.pitch = (v[0] + 63) / 64 * 64;
+            s.dtype = v[3]; s.aa = v[4]; s.gy = v[5] ? 1e-6 : 0.0;
+            s.f[0] = mem[0]; s.f[1] = mem[1];
+            s.fluid_frac = fluid; s.interior_frac = fluid == 1.0;
+            printf("%d\n", lbm3::pair_supported3(s) ? 1 : 0);
+        }
+        return 0;
+    }
     if (argc > 1) {
         int v[8], left;
         double fluid;
@@ -183,9 +197,21 @@ TAILS = [
 ]
 
 
-def _ask(driver, cases):
+# D3Q19: (nx, ny, nz, type, AA, force, fluid fraction), whether pairs were the faster side
+PAIRS = [
+    ((96, 80, 64, F32, 0, 1, 0.1), 0), ((96, 80, 64, F32, 0, 1, 0.6), 1),
+    ((96, 80, 64, F64, 0, 1, 0.1), 1), ((128, 128, 128, F32, 0, 1, 0.1), 1),
+    ((96, 80, 64, F64, 1, 1, 0.1), 0), ((96, 80, 64, F32, 1, 1, 0.6), 0),
+    ((128, 128, 128, F64, 1, 1, 0.3), 0), ((128, 128, 128, F64, 1, 1, 0.6), 1),
+    ((128, 128, 128, F32, 1, 1, 0.1), 0), ((256, 256, 128, F64, 1, 1, 0.1), 0),
+    ((256, 256, 128, F32, 1, 1, 0.1), 0), ((256, 256, 128, F32, 1, 1, 0.6), 1),
+    ((256, 256, 256, F32, 0, 0, 1.0), 1), ((96, 80, 64, F32, 1, 0, 1.0), 1),
+]
+
+
+def _ask(driver, cases, what="ask"):
     text = "\n".join(" ".join(map(str, c)) for c in cases)
-    r = subprocess.run([driver, "ask"], input=text, capture_output=True, text=True, check=True)
+    r = subprocess.run([driver, what], input=text, capture_output=True, text=True, check=True)
     return [list(map(int, line.split())) for line in r.stdout.split("\n") if line]
 
 
@@ -198,3 +224,8 @@ def test_faster_side_is_taken(driver):
 def test_short_rests_take_the_faster_side(driver):
     got = _ask(driver, [c for c, _ in TAILS])
     assert [(c, g[1]) for (c, _), g in zip(TAILS, got)] == TAILS
+
+
+def test_pairs_take_the_faster_side(driver):
+    got = _ask(driver, [c for c, _ in PAIRS], "3")
+    assert [(c, g[0]) for (c, _), g in zip(PAIRS, got)] == PAIRS
