@@ -40,6 +40,8 @@ _hook_active = False
 _LEND_BYTES = 4 << 30
 _LEND_FREE = 0.5
 _LEND_SMALL = 64 << 20
+# Calls of no more steps than this never borrow, so they do not ask either.
+_FEW_STEPS = 3
 
 
 def _spare(nbytes):
@@ -288,7 +290,7 @@ class Lattice:
         self._check(self._lib.lbm_set_graph_steps(self._ctx, int(steps)))
 
     def step(self, n=1):
-        if self.layout == "dense_aa" and not self.in_place:
+        if n > _FEW_STEPS and self.layout == "dense_aa" and not self.in_place:
             _step_aa(self, int(n), self._lib.lbm_step_scratch_bytes, self._lib.lbm_step_scratch)
         else:
             self._check(self._lib.lbm_step(self._ctx, int(n)))
@@ -494,7 +496,7 @@ class Lattice3D:
         self._check(self._lib.lbm3d_set_bounce_back(self._ctx, int(m)))
 
     def step(self, n=1):
-        if self.layout == "dense_aa" and not self.in_place:
+        if n > _FEW_STEPS and self.layout == "dense_aa" and not self.in_place:
             _step_aa(self, int(n), self._lib.lbm3d_step_scratch_bytes,
                      self._lib.lbm3d_step_scratch)
         else:

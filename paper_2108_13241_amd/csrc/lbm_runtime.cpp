@@ -903,6 +903,10 @@ static int step_impl(lbm_ctx *c, int64_t n, void *scratch)
 {
     if (n < 0)
         return fail(c, LBM_ERR_INVALID, "n must be >= 0");
+    if (n == 1) {  // programs that step one at a time: nothing to plan
+        LBM_HIP(c, step_group(c, c->s.stream, 1));
+        return LBM_OK;
+    }
     const int32_t G = graph_length(c, scratch);
     if (G >= 2 && c->graph_len != 0 && c->graph_len != G)
         drop_graphs(c);
