@@ -10,9 +10,10 @@ protocol is 100 warm-up + 1000 timed kernel calls).  One JSON line on stdout:
   roofline  = bytes of one pass over the lattice ((18 * pop_bytes + 1) per fluid node),
               which a kernel launch makes for up to STEPS_PER_LAUNCH steps, / average
               launch duration from HIP events on the stream the kernels run on, against
-              the MI355X HBM peak (8 TB/s).  "frac_of_peak" of a row (and
-              hbm_frac_of_peak) counts those bytes once per step instead, as every step
-              had its own pass: above 1 it is what several steps per pass save;
+              the MI355X HBM peak (8 TB/s).  "single_step_gbps" and "frac_of_peak" of a
+              row (and hbm_frac_of_peak) count those bytes once per step instead, as if every
+              step had its own pass: the rate that single steps would need, not what the
+              memory moves; above the peak it is what several steps per pass save;
   cpu_baseline = the FP64 CPU oracle on the host cores, a bounded number of steps of
               the same 4096^2 workload (about 12 s), plus one step on a single thread;
   variants  = the same measurement for the other storage types (16-bit rows with their
@@ -30,9 +31,9 @@ protocol is 100 warm-up + 1000 timed kernel calls).  One JSON line on stdout:
               node-list layouts, time per fluid node against the dense all-fluid step); with
               --suite full also 1024^2 / 2048^2, full-way walls, set-up and view costs and
               the adjoint at 4096^2.
-  Each variant states the warm-up it ran ("warmup_steps"): lattices small enough to replay
-  their steps as HIP graphs warm up by at least 64 steps, so that the graphs are captured
-  before the timed region.
+  Each variant states the warm-up it ran ("warmup_steps"): small lattices warm up by at least
+  64 steps, so that those that replay their steps as HIP graphs have captured them before
+  the timed region.
 
   --suite porous: the headline, the FP32 dense step and the 4096^2 porous-disc rows only
               (the sparse layouts' profiling workload).
@@ -134,6 +135,22 @@ def time_steps(lat, steps, warmup, min_warmup=0):
     return ms / 1e3, ms / max(steps, 1), warm
 
 
+def time_single_steps(lat, steps, warmup):
+    """Per-step ms of `steps` calls of one step (one launch each), with HIP events."""
+    import torch
+    for _ in range(warmup):
+        lat.step(1)
+    torch.cuda.synchronize()
+    t0 = torch.cuda.Event(enable_timing=True)
+    t1 = torch.cuda.Event(enable_timing=True)
+    t0.record()
+    for _ in range(steps):
+        lat.step(1)
+    t1.record()
+    torch.cuda.synchronize()
+    return t0.elapsed_time(t1) / max(steps, 1)
+
+
 def device_velocity(lat):
     """(u_x, u_y) of a D2Q9 lattice as device FP64 tensors [ny, nx] (solid nodes 0)."""
     import torch
@@ -198,7 +215,7 @@ def measure_dense(lbm, n, dtype, layout, steps, warmup, fields, trt=0.0, mrt=Non
         (" MRT s_e,s_eps,s_q=" + ",".join(f"{v:g}" for v in mrt) if mrt is not None else "")
     row = {"workload": f"taylor-green {n}^2" + model,
            "dtype": dtype, "layout": layout,
-           "glups": glups, "ms_per_step": ms, "hbm_gbps": glups * bpn,
+           "glups": glups, "ms_per_step": ms, "single_step_gbps": glups * bpn,
            "frac_of_peak": glups * bpn / HBM_PEAK_GBPS,
            "paper_U_B_bytes": 18 * POP_BYTES[dtype], "bytes_per_node": bpn,
            "steps": steps, "warmup_steps": warm, **extra}
@@ -237,7 +254,7 @@ def measure_d3q19(lbm, n, dtype, steps, warmup, layout="dense_ab", mrt=None, ref
     bpn = 38 * POP_BYTES[dtype] + 1
     row = {"workload": f"d3q19 taylor-green {n}^3" + (" MRT" if mrt is not None else ""),
            "dtype": dtype, "layout": layout,
-           "glups": glups, "ms_per_step": ms, "hbm_gbps": glups * bpn,
+           "glups": glups, "ms_per_step": ms, "single_step_gbps": glups * bpn,
            "frac_of_peak": glups * bpn / HBM_PEAK_GBPS, "bytes_per_node": bpn,
            "steps": steps, "warmup_steps": warm, **extra}
     return (row, u) if keep else row
@@ -558,8 +575,8 @@ def measure_adjoint(lbm, steps=200, T=2000):
     """Adjoint cost on the 1024 x 256 channel with a drag field, FP32.
 
     adjoint_over_forward: one adjoint step (adjoint kernel + its dJ/dg partial reduction) per
-    host call against one forward step per host call (graph replay off, so both pay the same
-    launch path).  checkpointed_*: the drivers as a user runs them, T steps with checkpoints
+    host call against one forward step per host call, so both pay the same launch path;
+    forward_fused_ms_per_step: forward steps in one call (several per launch).  checkpointed_*: the drivers as a user runs them, T steps with checkpoints
     every K = ceil(sqrt(T)) (forward with checkpoint copies; backward = segment recompute +
     adjoint), whole-run wall time on the device."""
     import torch
@@ -570,10 +587,8 @@ def measure_adjoint(lbm, steps=200, T=2000):
     alpha = synthetic.brinkman_alpha(nx, ny, seed=7, sigma=8.0).astype(np.float32)
     lat = lbm.Lattice(m, 0.8, force=(1e-5, 0.0), dtype="f32", layout="dense_ab")
     lat.set_porosity(alpha)
-    lat.set_graph_steps(0)
-    fwd_s, fwd_ms, _ = time_steps(lat, steps, 20)
-    lat.set_graph_steps(-1)
-    _, fwd_graph_ms, _ = time_steps(lat, steps, 64)
+    fwd_ms = time_single_steps(lat, steps, 20)
+    _, fused_ms, _ = time_steps(lat, steps, 64)
     sb = lat.state_bytes()
     state = torch.empty(sb, dtype=torch.uint8, device="cuda")
     lat.save_state(state)
@@ -618,7 +633,7 @@ def measure_adjoint(lbm, steps=200, T=2000):
     lat.close()
     del ckpt, seg
     return {"workload": "channel 1024x256 with drag field, f32", "forward_ms_per_step": fwd_ms,
-            "forward_graph_replay_ms_per_step": fwd_graph_ms,
+            "forward_fused_ms_per_step": fused_ms,
             "adjoint_ms_per_step": adj_ms, "adjoint_over_forward": adj_ms / fwd_ms,
             "checkpointed_T": T, "checkpointed_K": K,
             "checkpointed_forward_ms": run_ms, "checkpointed_backward_ms": back_ms,
@@ -626,7 +641,7 @@ def measure_adjoint(lbm, steps=200, T=2000):
 
 
 def measure_adjoint_large(lbm, n=4096, steps=50):
-    """Adjoint kernel against the forward step at a size where both are HBM-bound: n x n
+    """Adjoint kernel against the single forward step at a size where both are HBM-bound: n x n
     channel with a drag field, FP32 state.  Algorithmic bytes per fluid node: forward 77
     (18 x 4 + type + alpha), adjoint 129 (state 36 + lambda in 36 + lambda out 36 + alpha 4 +
     type 1 + FP64 gradient read-modify-write 16)."""
@@ -637,7 +652,7 @@ def measure_adjoint_large(lbm, n=4096, steps=50):
     alpha = synthetic.brinkman_alpha(n, n, seed=7, sigma=8.0).astype(np.float32)
     lat = lbm.Lattice(m, 0.8, force=(1e-5, 0.0), dtype="f32", layout="dense_ab")
     lat.set_porosity(alpha)
-    fwd_s, fwd_ms, _ = time_steps(lat, steps, 10)
+    fwd_ms = time_single_steps(lat, steps, 10)
     state = torch.empty(lat.state_bytes(), dtype=torch.uint8, device="cuda")
     lat.save_state(state)
     ab, _ = lat.adjoint_bytes()
@@ -738,7 +753,7 @@ def main():
     head = measure_dense(lbm, n, "f64", "dense_ab", args.steps, args.warmup, fields, keep=keep)
     if keep:
         head, u64 = head
-    log(f"[bench]   {head['glups']:.2f} GLUPS, {head['hbm_gbps']:.0f} GB/s")
+    log(f"[bench]   {head['glups']:.2f} GLUPS, {head['single_step_gbps']:.0f} GB/s if every step had its own pass")
     variants = []
     if args.suite == "sparse":
         variants.extend(sparse_study(lbm, n, max(args.steps // 5, 20), max(args.warmup // 5, 5)))
