@@ -31,7 +31,8 @@ protocol is 100 warm-up + 1000 timed kernel calls).  One JSON line on stdout:
               node-list layouts, time per fluid node against the dense all-fluid step); with
               --suite full also 1024^2 / 2048^2, full-way walls, set-up and view costs and
               the adjoint at 4096^2.
-  Each variant states the warm-up it ran ("warmup_steps"): small lattices warm up by at least
+  The line holds each variant's result and errors; --details FILE writes the rows in full.
+  There each variant states the warm-up it ran ("warmup_steps"): small lattices warm up by at least
   64 steps, so that those that replay their steps as HIP graphs have captured them before
   the timed region.
 
@@ -45,6 +46,7 @@ protocol is 100 warm-up + 1000 timed kernel calls).  One JSON line on stdout:
 
 Usage: python bench.py [--gpus 1] [--steps 1000] [--warmup 100]
                        [--suite default|full|headline|porous|sparse|spheres3]
+                       [--details FILE]
 """
 from __future__ import annotations
 
@@ -680,6 +682,24 @@ def measure_adjoint_large(lbm, n=4096, steps=50):
             "adjoint_frac_of_peak": nf * 129 / (adj_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS}
 
 
+# What a row is measured by (the first it has), and the errors stated beside it.
+_RESULTS = ("glups", "glups_per_fluid_node", "gbps", "adjoint_over_forward",
+            "us_per_step_launch_per_step", "glups_incl_host_transfers", "ms_per_step")
+_ERRORS = ("l2_err_vs_fp64", "l2_err_vs_closed_form", "mass_drift", "checkpointed_backward_ms")
+
+
+def short_variants(rows):
+    """{workload: {"dtype layout": {result, errors}}} with four digits: the whole line has to
+    fit what is commonly kept of a program's output (rows in full: --details)."""
+    out = {}
+    for row in rows:
+        result = next((k for k in _RESULTS if k in row), None)
+        keys = ([result] if result else []) + [k for k in _ERRORS if k in row]
+        name = " ".join(str(row[k]) for k in ("dtype", "layout") if k in row)
+        out.setdefault(row["workload"], {})[name] = {k: float(f"{row[k]:.4g}") for k in keys}
+    return out
+
+
 def _cpu_model():
     try:
         for line in open("/proc/cpuinfo"):
@@ -728,6 +748,7 @@ def main():
     ap.add_argument("--size", type=int, default=4096)
     ap.add_argument("--suite", default="default",
                     choices=["default", "full", "headline", "porous", "sparse", "spheres3"])
+    ap.add_argument("--details", metavar="FILE", help="write the variants' rows in full")
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--copy-reps", type=int, default=20)
     args = ap.parse_args()
@@ -933,9 +954,12 @@ def main():
                                f"tau=0.6, dense A-B layout, FP64 populations",
                    "nodes": n * n, "layout": "dense_ab", "tau": 0.6},
         "hbm_frac_of_peak": head["frac_of_peak"],
-        "roofline": roofline, "cpu_baseline": cpu, "variants": variants,
+        "roofline": roofline, "cpu_baseline": cpu, "variants": short_variants(variants),
         "paper_context": PAPER_CONTEXT,
     }
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump({**out, "variants": variants}, f, indent=1)
     print(json.dumps(out), flush=True)
 
 

@@ -1,6 +1,7 @@
 """What bench.py's rows say: a rate at which single steps would move memory is not called memory
 bandwidth, and the adjoint's forward reference is one step per launch, as an adjoint step is."""
 import importlib.util
+import json
 import os
 import sys
 
@@ -28,6 +29,23 @@ def test_forward_reference_is_single_steps(bench, name):
     body = _times(open(bench.__file__).read(), name)
     assert "fwd_ms = time_single_steps(" in body
     assert "graph" not in body
+
+
+def test_line_is_short(bench):
+    """A default run has 52 variants, whose rows in full made a line of 21 KB; of a program's
+    output, its log included, 13 KB are commonly kept."""
+    rows = [{"workload": f"reduced precision: porous discs 4096^2 phi=0.5, {k} steps", "dtype": dt,
+             "layout": "dense_ab", "glups": 123.456789 + k, "ms_per_step": 0.1234567,
+             "mass_drift": -1.23456789e-13, "l2_err_vs_fp64": 0.00123456789,
+             "l2_err_reference": "FP64 HIP path, same layout and step count", "steps": 5000}
+            for k in range(13) for dt in ("f64", "f32", "f16s", "bf16s")]
+    short = bench.short_variants(rows)
+    assert sum(len(v) for v in short.values()) == len(rows)
+    assert short[rows[5]["workload"]]["f32 dense_ab"]["glups"] == 124.5
+    assert len(json.dumps(short)) < 6000
+    # rows without a rate of their own keep their time
+    assert bench.short_variants([{"workload": "w", "ms_per_step": 2.0}]) == {
+        "w": {"": {"ms_per_step": 2.0}}}
 
 
 @pytest.mark.gpu
