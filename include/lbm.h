@@ -257,10 +257,11 @@ int lbm_step_scratch(lbm_ctx *ctx, int64_t n, void *scratch, size_t bytes);
  * consecutive steps as one captured graph (captured once, on a private stream,
  * and replayed on the context's stream; bitwise-identical results).  -1 = auto
  * (32 steps for lattices that move less than 128 MB per step and run one launch per
- * step, where host launch overhead is a visible share of a step; else off), 0 = off, or an even count in
- * [2, 4096].  The first replay from each parity captures and instantiates its
- * graph (a one-time cost of a few ms).  Changing the force, the drag field or
- * the open boundaries discards captured graphs. */
+ * step, where host launch overhead is a visible share of a step; else off), 0 = off,
+ * or an even count in [2, 4096].  While the context's stream is being captured the steps
+ * are recorded one launch after the other.  The first replay from each parity
+ * captures and instantiates its graph (a one-time cost of a few ms).  Changing the
+ * force, the drag field or the open boundaries discards captured graphs. */
 int lbm_set_graph_steps(lbm_ctx *ctx, int32_t steps);
 
 /* Macroscopic fields (Eq. 2, with the half-force / drag velocity) of the

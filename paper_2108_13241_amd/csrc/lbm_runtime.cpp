@@ -98,11 +98,16 @@ int fail(lbm_ctx *c, int status, const std::string &msg)
     return status;
 }
 
-void note_capture(const lbm_ctx *c)
+bool is_capturing(const lbm_ctx *c)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (!c->recorded && c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
-        st != hipStreamCaptureStatusNone)
+    return c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
+           st != hipStreamCaptureStatusNone;
+}
+
+void note_capture(const lbm_ctx *c)
+{
+    if (!c->recorded && is_capturing(c))
         c->recorded = true;
 }
 
@@ -735,13 +740,6 @@ int lbm_set_force(lbm_ctx *c, const double *force)
     return LBM_OK;
 }
 
-static bool is_capturing(const lbm_ctx *c)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return c->s.stream && hipStreamIsCapturing(c->s.stream, &st) == hipSuccess &&
-           st != hipStreamCaptureStatusNone;
-}
-
 // The lattices that launch_steps works on: the layout's own two, or DENSE_AA's one and a
 // lattice the caller lends for the call (null: steps in place).
 static lbm::DevState fused_state(const lbm_ctx *c, void *scratch)
@@ -907,7 +905,8 @@ static int step_impl(lbm_ctx *c, int64_t n, void *scratch)
         LBM_HIP(c, step_group(c, c->s.stream, 1));
         return LBM_OK;
     }
-    const int32_t G = graph_length(c, scratch);
+    // a caller's graph takes the steps themselves: HIP does not record the launch of a graph
+    const int32_t G = is_capturing(c) ? 0 : graph_length(c, scratch);
     if (G >= 2 && c->graph_len != 0 && c->graph_len != G)
         drop_graphs(c);
     while (G >= 2 && n >= G) {
