@@ -703,6 +703,14 @@ __device__ __forceinline__ void tile_node(uint32_t s, int &lx, int &ly)
     ly = (int)(((s >> 2) & 3u) | ((s >> 4) & 12u));
 }
 
+// Whether the 128-byte line of lane l's slot holds a fluid node's.
+template <class M>
+__device__ __forceinline__ bool line_has_fluid(uint64_t fluid, uint32_t l)
+{
+    constexpr uint32_t G = 128u / (uint32_t)sizeof(M);
+    return ((fluid >> (l & ~(G - 1u))) & ((uint64_t(1) << G) - 1u)) != 0;
+}
+
 template <class ST, int PH>
 __global__ __launch_bounds__(kTileNodes) void k_step_tiled(
     const typename ST::mem *__restrict__ src, typename ST::mem *__restrict__ dst,
@@ -769,10 +777,7 @@ __global__ __launch_bounds__(kTileNodes) void k_step_tiled(
             // whole.  Lines left partly written cost the memory system more than
             // the extra bytes (measured: 8 % / 14 % faster at fluid fraction 0.5;
             // 256- or 512-byte granules and the 2-byte types gain nothing).
-            constexpr uint32_t G = 128u / (uint32_t)sizeof(M);
-            const uint32_t l = s & 63u;
-            const uint64_t gm = (fm >> (l & ~(G - 1u))) & ((uint64_t(1) << G) - 1u);
-            if (gm) {
+            if (line_has_fluid<M>(fm, s & 63u)) {
 #pragma unroll
                 for (int i = 0; i < 9; ++i)
                     store_nt(&dst[(uint32_t)i * kTileStride + own], M(0));
@@ -812,6 +817,21 @@ __global__ __launch_bounds__(kTileNodes) void k_step_tiled(
 #pragma unroll
     for (int i = 0; i < 9; ++i)
         store_nt(&dst[(uint32_t)i * kTileStride + own], ST::st(f[i], i));
+}
+
+// The placeholders of k_step_tiled by themselves (FP64; in the deviation types the value of
+// the rest state is the placeholder already).  Once per lattice after it was initialised
+// or loaded.
+__global__ __launch_bounds__(kTileNodes) void k_placeholders(double *__restrict__ lattice,
+                                                             const TileMeta *__restrict__ meta)
+{
+    const uint32_t s = threadIdx.x, l = s & 63u;
+    const uint64_t fm = meta[blockIdx.x].fluid[s >> 6];
+    if (((fm >> l) & 1u) || !line_has_fluid<double>(fm, l))
+        return;
+    const uint32_t own = tile_base(blockIdx.x, s);
+    for (int i = 0; i < 9; ++i)
+        lattice[(uint32_t)i * kTileStride + own] = 0.0;
 }
 
 // ---------------------------------------------------------- step: indirect --
@@ -1691,6 +1711,14 @@ hipError_t launch_rest(const DevState &s, void *lattice)
     case kBF16S: k_rest<BF16S><<<(uint32_t)blocks, kBlock, 0, s.stream>>>((BF16S::mem *)lattice, n, run); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_placeholders(const DevState &s, void *lattice)
+{
+    if (s.n_tiles > 0)
+        k_placeholders<<<(uint32_t)s.n_tiles, kTileNodes, 0, s.stream>>>((double *)lattice,
+                                                                        s.tile_meta);
     return hipGetLastError();
 }
 

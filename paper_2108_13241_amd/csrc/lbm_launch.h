@@ -181,6 +181,8 @@ hipError_t launch_scatter_canonical(const DevState &s, int64_t t, int cur, const
 // Rest state (rho = 1, u = 0) straight into one stored lattice (all 9 * plane
 // slots), without a canonical staging buffer.
 hipError_t launch_rest(const DevState &s, void *lattice);
+// FP64 tiles: what a single step stores in the solid slots of a lattice (k_step_tiled).
+hipError_t launch_placeholders(const DevState &s, void *lattice);
 // Equilibrium (Eq. 6) from device FP64 [ny][nx] fields (null = rest) -> fc.
 hipError_t launch_equilibrium(const DevState &s, const double *rho, const double *ux,
                               const double *uy, double *fc);

@@ -82,6 +82,8 @@ struct lbm_ctx {
     // step(n) leaves the state in the buffer that n single steps would, so that
     // the graph finds it there whatever runs between its replays.
     mutable bool recorded = false;
+    // FP64 tiles: the lattice's solid slots hold what single steps leave there.
+    bool placed[2] = {false, false};
     // Overlapped checkpointed adjoint: a second segment buffer (library-owned),
     // an auxiliary stream for the segment recomputation and its events.
     void *seg2 = nullptr;
@@ -215,6 +217,7 @@ int init_state(lbm_ctx *c, const double *rho, const double *ux, const double *uy
         // bounce-back slots in the other lattice
         c->t = 0;
         c->cur = 0;
+        c->placed[0] = c->placed[1] = false;
         LBM_HIP(c, lbm::launch_rest(c->s, c->s.f[0]));
         if (c->s.f[1])
             LBM_HIP(c, lbm::launch_rest(c->s, c->s.f[1]));
@@ -769,7 +772,15 @@ static hipError_t step_group(lbm_ctx *c, hipStream_t stream, int steps)
 {
     lbm::DevState s = c->s;
     s.stream = stream;
-    hipError_t e = steps > 1 ? lbm::launch_steps(s, c->cur, steps) : lbm::launch_step(s, c->t, c->cur);
+    hipError_t e = hipSuccess;
+    // A fused launch writes fluid slots only; raw states are to be those of single steps, which
+    // also write solid ones.  (A captured pass runs with the graph, not now.)
+    if (steps > 1 && s.layout == LBM_TILED16 && s.dtype == LBM_F64 && !c->placed[1 - c->cur]) {
+        e = lbm::launch_placeholders(s, s.f[1 - c->cur]);
+        c->placed[1 - c->cur] = stream == c->s.stream && !is_capturing(c);
+    }
+    if (e == hipSuccess)
+        e = steps > 1 ? lbm::launch_steps(s, c->cur, steps) : lbm::launch_step(s, c->t, c->cur);
     if (c->s.layout != LBM_DENSE_AA)
         c->cur ^= 1;
     c->t += steps;
@@ -1092,6 +1103,7 @@ int lbm_load_state(lbm_ctx *c, const void *dev_src)
     size_t b = 0;
     lbm_state_bytes(c, &b);
     LBM_HIP(c, hipMemcpyAsync(state_lattice(c), dev_src, b, hipMemcpyDeviceToDevice, c->s.stream));
+    c->placed[c->cur] = false;
     return LBM_OK;
 }
 
