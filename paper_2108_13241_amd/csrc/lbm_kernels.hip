@@ -1524,10 +1524,11 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
 //   896^2 7.0 / 7.8 (0.8), 1200^2 12.1 / 13.0 (0.8), 14.4 / 13.0 (0.95), 3008^2 47 / 48 and 61 /
 //   60 (0.8), 4096^2 140 / 104 (0.9), MRT 1200^2 13.1 / 18.2 (0.8).
 //   TILED16 is alike.  MRT with a force in FP64, six steps: INDIRECT 704 x 688 6.6 / 9.6
-//   (0.4) and 12.4 / 9.5 (0.7), 1504^2 26.6 / 28.7 (0.4) and 42.8 / 28.7 (0.7).
+//   (0.4) and 12.4 / 9.5 (0.7), 1504^2 26.6 / 28.7 (0.4) and 42.8 / 28.7 (0.7), 512 x 480 4.9 /
+//   5.4 (0.6); TRT and drag 512 x 480 3.8 / 4.3 (0.3).
 //   Dense, 16 bits: 896^2 with a force 7.2 / 8.5, 640^2 5.4 / 4.5; MRT and force 2048^2 32 /
 //   39, MRT 1200^2 11.0 / 12.2 (AA); open boundaries 1200^2 10.8 / 15.5 (AA), 14.6 / 15.1.  AA
-//   in FP64 with open boundaries 640^2 9.5 / 10.4.
+//   with open boundaries in FP64 640^2 9.5 / 10.4, in FP32 with MRT 992 x 704 8.1 / 8.5.
 // A single step of a dense lattice skips the wavefronts and segments without fluid nodes, and
 // the AA layout's writes one lattice less, so single steps of mostly solid lattices win
 // there too (fluid fraction 0.1 and 0.25, 704 x 688 / 4096^2, with a force, six or eight steps):
@@ -1554,7 +1555,7 @@ static bool fused_pays(const DevState &s, int k, int64_t blocks)
     double least;  // fluid fraction
     if (sparse) {
         if (f64)
-            least = few ? 0.0
+            least = few ? (s.mrt ? 0.7 : 0.4)
                         : s.mrt ? (nodes < 700000 ? 0.58 : 0.46)
                                 : nodes < 700000 ? 0.5 : list ? 0.35 : 0.34;
         else if (f32)
@@ -1568,6 +1569,8 @@ static bool fused_pays(const DevState &s, int k, int64_t blocks)
                 return false;
             least = aa ? (heavy ? 0.38 : 0.22) : heavy ? 0.25 : 0.19;
         } else if (f32) {
+            if (aa && s.open && s.mrt && nodes < 1000000)
+                return false;
             least = aa ? (heavy ? 0.45 : 0.22) : !heavy ? 0.08 : nodes < 1000000 ? 0.4 : 0.22;
         } else if (few) {
             least = 0.0;
@@ -1622,19 +1625,30 @@ static bool uneven_fours(const DevState &s)
 // 1.05 / 1.13, FP32 0.55 1.11 / 0.75, 704 x 688 1.28 / 1.03; dense 4096^2 FP16 with walls and a
 // force 1.10 / 0.87, FP64 0.25 0.94 / 0.74, FP32 0.1 1.15 / 0.94, MRT FP32 704 x 688 0.4 1.07 / 0.90,
 // 0.7 0.97 / 0.83.  On squares that fill the chip once two steps take 0.6 to 0.9 of two
-// launches (304 x 208; TILED16 in FP32 1.1).
+// launches (304 x 208; TILED16 in FP32 1.1; open boundaries in FP64 1.3 / 0.95, MRT on INDIRECT
+// 1.4 / 1.1).  The AA layout's launches come in twos: 2 + 2 steps against four in place take
+// 0.65 to 0.9 in FP64 and FP32, with open boundaries, TRT, MRT or 16 bits 1.1 to 1.2.  Five steps
+// of six still lose in FP32 with MRT on sparse layouts (1.08 at 0.9), in BF16 with MRT (4096 x 2048
+// 1.12) and on tiles with open boundaries (1.10).
 static int least_steps(const DevState &s)
 {
     int n = 0;
     const int k = square_steps(s.nx, s.ny, s.dtype, n);
     const bool one_round = k && square_blocks(s.nx, s.ny, n, k) <= 256;
     const bool f64 = s.dtype == kF64, f32 = s.dtype == kF32;
+    const bool sparse = s.layout == kTiled16 || s.layout == kIndirect;
+    if (!one_round && ((sparse && f32 && s.mrt) || (!f64 && !f32 && (s.mrt || (sparse && s.open)))))
+        return 6;
+    if (s.layout == kDenseAA && (s.open || s.trt || s.mrt || !(f64 || f32)))
+        return 4;
     if (s.layout == kTiled16)
         return one_round || (f64 && s.fluid_frac >= 0.7) ? 3 : 4;
     if (one_round)
-        return 2;
+        return !s.open ? 2 : f64 && s.mrt && sparse ? 4 : 3;
     if (s.layout == kIndirect)
-        return s.fluid_frac < 0.7 || (f32 && s.mrt) ? 4 : f64 ? 2 : 3;
+        return s.fluid_frac < 0.7 ? 4 : f64 && !s.open ? 2 : 3;
+    if (k && s.mrt)  // squares, 512 x 480: 1.07 to 1.13
+        return 3;
     return (f64 || f32) && s.fluid_frac >= (heavy_collision(s) ? 0.6 : 0.4) ? 2 : 3;
 }
 

@@ -41,6 +41,8 @@ MEASURED = [
     ((4096, 4096, F16, AA, 1, 0, 0, 0, 0.1), False), ((4096, 4096, F16, AA, 1, 0, 0, 0, 0.4), True),
     ((704, 688, F64, LIST, 1, 0, 0, 2, 0.55), False), ((704, 688, F64, LIST, 1, 0, 0, 2, 0.7), True),
     ((1504, 1504, F64, LIST, 1, 0, 0, 2, 0.4), False), ((1504, 1504, F64, LIST, 1, 0, 0, 0, 0.4), True),
+    ((512, 480, F64, LIST, 1, 0, 0, 1, 0.3), False), ((512, 480, F64, LIST, 1, 1, 0, 0, 0.3), False),
+    ((512, 480, F64, LIST, 1, 0, 0, 2, 0.6), False), ((512, 480, F64, LIST, 1, 0, 0, 1, 0.6), True),
     ((4096, 4096, F64, TILED, 1, 0, 0, 0, 0.25), False), ((4096, 4096, F64, TILED, 1, 0, 0, 0, 0.4), True),
 ]
 
@@ -55,6 +57,9 @@ TAILS = [
     ((4096, 4096, F64, AB, 0, 0, 0, 0, 1.0, 5), 5), ((4096, 4096, F64, AB, 0, 0, 0, 0, 1.0, 2), 2),
     ((4096, 4096, F32, AB, 1, 0, 0, 0, 0.1, 2), 1), ((256, 64, F32, LIST, 1, 0, 0, 0, 0.97, 2), 2),
     ((4096, 4096, F32, AB, 1, 0, 0, 0, 0.97, 100), 8),
+    ((240, 160, F64, AB, 0, 0, 1, 0, 1.0, 2), 1), ((240, 160, F64, LIST, 0, 0, 1, 2, 1.0, 3), 1),
+    ((2048, 1536, F32, LIST, 1, 1, 0, 2, 0.9, 5), 1), ((4096, 2048, F16, AB, 0, 0, 0, 2, 1.0, 5), 1),
+    ((4096, 2048, F16, TILED, 0, 0, 1, 0, 1.0, 5), 1), ((512, 480, F32, AB, 0, 0, 1, 2, 1.0, 2), 1),
 ]
 
 
