@@ -555,6 +555,11 @@ hipError_t steps_typed(const DevState &s, const void *first, const void *rest, s
 // workgroup per CU), four steps on larger lattices.  Measured at 3 / 4 / 5 / 6 steps, us
 // per step in FP32: 400 x 150 5.2 / 5.1 / 4.6 / 5.2, 700 x 200 6.2 / 6.9 / 7.0 / 6.8, 1024 x
 // 256 11.0 / 10.4 / 11.3 / 11.7, 900^2 29.9 / 30.3 / 31.9 / 33.3.
+// Several rounds pay while the squares' extra nodes cost less than a single step's memory
+// traffic, which skips rows without fluid nodes (fluid fraction 1 / 0.6 / 0.2, ms of 200
+// backward steps with their recomputation, single -> squares): FP32 900^2 6.4 -> 5.7, 5.0 -> 5.2,
+// 3.9 -> 4.5; 1024 x 256 2.41 -> 1.99, 2.06 -> 1.86, 1.98 -> 1.57; FP64 1024 x 256 4.24 -> 3.45, 3.17
+// -> 3.14, 2.55 -> 2.96.
 int adjoint_square_steps(const DevState &s)
 {
     int n = 0;
@@ -565,7 +570,8 @@ int adjoint_square_steps(const DevState &s)
         if ((int64_t)((s.nx + out - 1) / out) * ((s.ny + out - 1) / out) <= 256)
             return k;
     }
-    return 4;
+    const double least = s.dtype == kF64 ? 0.6 : (int64_t)s.nx * s.ny < 400000 ? 0.0 : 0.7;
+    return s.fluid_frac >= least ? 4 : 1;
 }
 
 int64_t adjoint_run_partials(const DevState &s)

@@ -47,6 +47,14 @@ int main(int argc, char **argv)
         }
         return 0;
     }
+    // "adjoint": nx ny dtype fluid, the reverse steps a launch takes
+    if (argc > 1 && !strcmp(argv[1], "adjoint")) {
+        int v[3];
+        double fluid;
+        while (scanf("%d%d%d%lf", v, v + 1, v + 2, &fluid) == 4)
+            printf("%d\n", adjoint_square_steps(state(v[0], v[1], v[2], 0, 1, 1, 0, 0, fluid)));
+        return 0;
+    }
     if (argc > 1) {
         int v[8], left;
         double fluid;

@@ -89,3 +89,12 @@ def test_short_rests_take_the_faster_side(driver):
 def test_pairs_take_the_faster_side(driver):
     got = fused_rules.ask(driver, [c for c, _ in PAIRS], "3")
     assert [(c, g[0]) for (c, _), g in zip(PAIRS, got)] == PAIRS
+
+
+def test_reverse_steps_take_the_faster_side(driver):
+    """(nx, ny, type, fluid fraction): whether squares were faster than single reverse steps."""
+    cases = [((200, 60, F64, 0.2), True), ((400, 150, F32, 0.2), True), ((1024, 256, F32, 0.2), True),
+             ((1024, 256, F64, 1.0), True), ((1024, 256, F64, 0.2), False), ((900, 900, F32, 1.0), True),
+             ((900, 900, F32, 0.6), False), ((900, 900, F32, 0.2), False), ((900, 900, F64, 1.0), False)]
+    got = fused_rules.ask(driver, [c for c, _ in cases], "adjoint")
+    assert [(c, g[0] > 1) for (c, _), g in zip(cases, got)] == cases
