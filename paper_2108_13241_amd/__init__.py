@@ -60,7 +60,8 @@ def _spare(nbytes):
 def _lend(stream, nbytes):
     """A block of torch's memory on `stream`, or None where there is none to spare."""
     import torch
-    if nbytes == 0:
+    # nothing is allocated inside a capture, of whatever stream
+    if nbytes == 0 or torch.cuda.is_current_stream_capturing():
         return None
     if torch.cuda.current_stream() != stream:
         with torch.cuda.stream(stream):

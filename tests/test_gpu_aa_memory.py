@@ -44,7 +44,9 @@ def make(lbm, shape, dtype, solid=True):
 def state(lat):
     import torch
     s = torch.zeros(lat.state_bytes(), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()  # the lattice may have a stream of its own
     lat.save_state(s)
+    torch.cuda.synchronize()
     return s
 
 
@@ -169,5 +171,33 @@ def test_captured_calls_borrow_nothing(lbm, shape):
     b.in_place = True
     b.step(total)
     assert np.array_equal(a.get_populations(), b.get_populations())
+    a.close()
+    b.close()
+
+
+def test_steps_beside_a_capture(lbm, monkeypatch):
+    """Steps of a lattice on its own stream while another stream is being captured: run, not
+    recorded, and without asking for memory."""
+    import torch
+    announce("AA steps beside a capture")
+    a, b = make(lbm, (611, 590), "f32"), make(lbm, (611, 590), "f32")
+    own, other = torch.cuda.Stream(), torch.cuda.Stream()
+    a.set_stream(own)
+    x = torch.zeros(1000, device="cuda")
+    torch.cuda.synchronize()
+    asked = []
+    real = torch.empty
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=other):
+        x += 1
+        monkeypatch.setattr(torch, "empty", lambda *p, **k: asked.append(p) or real(*p, **k))
+        a.step(20)
+        monkeypatch.undo()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert not asked and float(x.sum()) == 1000.0
+    b.in_place = True
+    b.step(20)
+    assert torch.equal(state(a), state(b))
     a.close()
     b.close()
