@@ -1,5 +1,5 @@
 // Device-side pieces shared by the dense D2Q9 step kernels (one step per launch
-// in lbm_kernels.hip, several in lbm_multistep.hip): lane moves, the physics
+// in lbm_kernels.hip, several in lbm_multistep.h): lane moves, the physics
 // variants and the kernels' arguments.
 #pragma once
 

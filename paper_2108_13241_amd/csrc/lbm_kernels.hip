@@ -1517,8 +1517,8 @@ hipError_t launch_step(const DevState &s, int64_t t, int cur)
 // fluid nodes only, and below some millions of nodes reads them from the memory-side
 // cache.  So the fewer bytes a node has and the more its collision costs, the later
 // fusing pays.  Measured, us per step, single / fused (discs, with a force):
-//   INDIRECT, fluid fraction 0.4 and 0.6: FP64 640^2 5.7 / 6.3 and 9.9 / 6.4 (0.68), 4096^2
-//   118 / 131 (0.2: 89 / 118) and 217 / 122; FP32 640^2 3.9 / 4.3 and 5.0 / 4.4 (0.68),
+//   INDIRECT, fluid fraction 0.4 and 0.6: FP64 704 x 688 6.4 / 7.7 and 8.0 / 7.7 (0.55), 4096^2
+//   174 / 148 (0.25: 110 / 144) and 234 / 148 (0.55); FP32 640^2 3.9 / 4.3 and 5.0 / 4.4 (0.68),
 //   896^2 5.1 / 7.4 and 7.5 / 7.5, 4096^2 113 / 97 (0.5); MRT 896^2 7.9 / 9.6 (0.6), 13.1 /
 //   9.8 (0.95), 2048^2 34 / 45 and 44 / 45 (0.8); 16 bits 400^2 3.8 / 2.9, 640^2 3.9 / 4.3,
 //   896^2 7.0 / 7.8 (0.8), 1200^2 12.1 / 13.0 (0.8), 14.4 / 13.0 (0.95), 3008^2 47 / 48 and 61 /

@@ -93,11 +93,11 @@ inline int64_t square_blocks(int nx, int ny, int n, int steps)
 // 16 x 16 nodes at four steps while that leaves at most one workgroup per CU; else
 // 32 x 32 at the most steps that do; else four steps, in FP64 up to two rounds of the
 // chip (one workgroup per CU: its LDS), in the narrower types up to three (two per CU).
-// Measured, us per step, FP64: 256 x 64 1.18 (16, 4 steps), 1.36 (32, 8 steps), strips
-// 2.15; 257^2 with a lid 1.64 (32, 6 steps), 2.06 (16, 3 steps), strips 2.75; 512^2
-// 3.9 (32, 4 steps), strips 4.0; FP32 128^2 0.99 (16, 4 steps), 1.02 (32, 8 steps); 400 x
+// Measured, us per step, FP64: 256 x 64 1.29 (16, 4 steps), 1.57 (32, 8 steps), strips
+// 2.56; 257^2 with a lid, TRT 2.03 (32, 6 steps), 2.53 (16, 3 steps), strips 3.8; 512^2 with a
+// force 4.5 (32, 4 steps), strips 5.0; FP32 128^2 0.99 (16, 4 steps), 1.02 (32, 8 steps); 400 x
 // 300 1.63 (32, 4 steps), 2.10 (16, 3 steps); 1024 x 256 with drag 2.98 (32, 4 steps), 3.4
-// (32, 6 steps), strips 4.0; with a force FP64 560^2 5.6, strips 4.9; FP32 760^2 5.0,
+// (32, 6 steps), strips 4.0; with a force FP64 560^2 6.3, strips 5.5; FP32 760^2 5.0,
 // strips 5.7, 900^2 6.9, strips 7.5.
 inline int square_steps(int nx, int ny, int dtype, int &n)
 {

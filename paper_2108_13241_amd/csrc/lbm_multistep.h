@@ -20,12 +20,13 @@
 // steps.  Boundary nodes: the node types travel with the rows; a row of interior
 // nodes (one ballot) skips the bounce-back selects.
 //
-// Measured, Taylor-Green 4096^2, us per step over calls of 48 steps (single
-// launches -> fused): FP64 390 -> 109 (8 steps a launch), FP32 190 -> 57, FP16 99 ->
-// 59, BF16 99 -> 64; with walls 114, 63, 59, 68; with a force 122, 88, 86, 92; MRT 111,
-// 83, 94, 100.  The FP32 and 16-bit kernels are bound by VALU issue (all of it:
-// 118 and 130 instructions a node and step, 4 cycles a wavefront each).  FP64 moves 2.5 GB a
-// launch (1.03 of one step's) in 860 us, 0.46 of the copy rate, and issues 54 % of the
+// Measured, 4096^2, us per step over calls of 48 steps (single launches -> fused): FP64
+// 388 -> 104 (8 steps a launch), FP32 190 -> 54, FP16 99 -> 58, BF16 99 -> 61; with walls
+// FP64 112, FP32 63; with a force and walls 134, 77, FP16 80; MRT 127, 81, FP16 91; TRT FP64 110;
+// drag FP64 140.  The FP32 and 16-bit kernels are bound by VALU issue (0.9 to 1.0 of its cycles:
+// 118 and 130 instructions a node and step, 4 cycles a wavefront each); with open boundaries
+// on 512 rows 0.5: strips of 40 rows spend 17 of 57 iterations filling and draining.  FP64 moves 2.5 GB a
+// launch (1.03 of one step's) in 830 us, 0.48 of the copy rate, and issues 61 % of the
 // VALU cycles: what is left is the barrier per row, which keeps the two from
 // overlapping fully.  A form that kept all K
 // steps in one wavefront (rows in registers, lane shifts instead of LDS) ran
@@ -507,8 +508,8 @@ __global__ __launch_bounds__(N *N) void k_steps_square(const DenseArgs<ST> k, co
         }
     };
     const int at = (int)threadIdx.x + L::kPad;
-    // wavefronts without boundary nodes skip the bounce-back selects (us per step: 257^2
-    // FP64 1.70 -> 1.58, 800^2 FP32 4.65 -> 4.48); in the variants that the branch made
+    // wavefronts without boundary nodes skip the bounce-back selects (us per step: 800^2
+    // FP32 4.65 -> 4.48, FP64 alike); in the variants that the branch made
     // slower (16 bits 512^2 2.55 -> 3.03, FP32 with drag 1024 x 256 3.08 -> 3.19) all select
     constexpr bool kSkip = sizeof(M) == 8 || (sizeof(M) == 4 && !DRAG);
     const bool walls = __ballot(nm != 0 && type != kSolid) != 0;
@@ -586,8 +587,8 @@ struct StepsShape {
 // waste least, but the grid should fill whole rounds of the chip: the time goes
 // with the iterations times the rounds, where a last round that leaves CUs partly
 // filled costs its share less 0.3 (one of two workgroups per CU: 0.65 of a full
-// round; FP64 4096^2: 1462 blocks, 3 rounds, 106 us per step; 1548 blocks, 114;
-// 1978, 107; 2064, 112).  Candidates: the strip lengths that end just under 1/2, 1,
+// round; FP64 4096^2: 1462 blocks, 3 rounds, 103 us per step; 1548 blocks, 112;
+// 1978, 103; 2064, 110).  Candidates: the strip lengths that end just under 1/2, 1,
 // 2 .. 8 rounds.
 inline int strip_rows(int ny, uint32_t nstrips, int K, int per_cu)
 {
