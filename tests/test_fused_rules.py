@@ -60,6 +60,7 @@ TAILS = [
     ((240, 160, F64, AB, 0, 0, 1, 0, 1.0, 2), 1), ((240, 160, F64, LIST, 0, 0, 1, 2, 1.0, 3), 1),
     ((2048, 1536, F32, LIST, 1, 1, 0, 2, 0.9, 5), 1), ((4096, 2048, F16, AB, 0, 0, 0, 2, 1.0, 5), 1),
     ((4096, 2048, F16, TILED, 0, 0, 1, 0, 1.0, 5), 1), ((512, 480, F32, AB, 0, 0, 1, 2, 1.0, 2), 1),
+    ((2048, 2048, F16, AB, 0, 0, 0, 0, 1.0, 2), 2),
 ]
 
 
