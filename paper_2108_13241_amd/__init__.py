@@ -291,10 +291,11 @@ class Lattice:
         self._check(self._lib.lbm_set_graph_steps(self._ctx, int(steps)))
 
     def step(self, n=1):
+        n = int(n)
         if n > _FEW_STEPS and self.layout == "dense_aa" and not self.in_place:
-            _step_aa(self, int(n), self._lib.lbm_step_scratch_bytes, self._lib.lbm_step_scratch)
+            _step_aa(self, n, self._lib.lbm_step_scratch_bytes, self._lib.lbm_step_scratch)
         else:
-            self._check(self._lib.lbm_step(self._ctx, int(n)))
+            self._check(self._lib.lbm_step(self._ctx, n))
 
     def macroscopic(self):
         out = [np.zeros((self.ny, self.nx)) for _ in range(3)]
@@ -497,11 +498,12 @@ class Lattice3D:
         self._check(self._lib.lbm3d_set_bounce_back(self._ctx, int(m)))
 
     def step(self, n=1):
+        n = int(n)
         if n > _FEW_STEPS and self.layout == "dense_aa" and not self.in_place:
-            _step_aa(self, int(n), self._lib.lbm3d_step_scratch_bytes,
+            _step_aa(self, n, self._lib.lbm3d_step_scratch_bytes,
                      self._lib.lbm3d_step_scratch)
         else:
-            self._check(self._lib.lbm3d_step(self._ctx, int(n)))
+            self._check(self._lib.lbm3d_step(self._ctx, n))
 
     def macroscopic(self):
         out = [np.zeros(self.shape) for _ in range(4)]

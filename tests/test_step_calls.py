@@ -24,3 +24,12 @@ def test_few_steps_are_one_call(cls, prefix, layout):
     for n in (0, 1, 2, 3):
         lat.step(n)
     assert lat._lib.calls == [f"{prefix}_step"] * 4
+
+
+@pytest.mark.parametrize("cls", [lbm.Lattice, lbm.Lattice3D])
+@pytest.mark.parametrize("n", ["5", 5.0, True])
+def test_counts_are_taken_as_int_takes_them(cls, n):
+    lat = cls.__new__(cls)
+    lat.layout, lat.in_place, lat._ctx, lat._lib = "dense_aa", True, None, Recorder()
+    lat.step(n)
+    assert len(lat._lib.calls) == 1
