@@ -201,3 +201,36 @@ def test_steps_beside_a_capture(lbm, monkeypatch):
     assert torch.equal(state(a), state(b))
     a.close()
     b.close()
+
+
+def test_threads_and_streams(lbm):
+    """Lattices stepped by threads of their own, on streams of their own: each borrows for itself."""
+    import threading
+
+    import torch
+    announce("AA lattices in four threads")
+    shapes = [(150, 50), (611, 590), (1216, 912), (65, 66, 128)]
+    lats = [make(lbm, s, "f32") for s in shapes]
+    want = [make(lbm, s, "f32") for s in shapes]
+    streams = [torch.cuda.Stream() for _ in shapes]
+    for lat, stream in zip(lats, streams):
+        lat.set_stream(stream)
+    torch.cuda.synchronize()
+    counts = [9, 20, 5, 16, 33, 8] * 3
+
+    def work(lat):
+        for n in counts:
+            lat.step(n)
+
+    threads = [threading.Thread(target=work, args=(lat,)) for lat in lats]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for lat, ref in zip(lats, want):
+        ref.in_place = True
+        ref.step(sum(counts))
+        assert torch.equal(state(lat), state(ref))
+        lat.close()
+        ref.close()
