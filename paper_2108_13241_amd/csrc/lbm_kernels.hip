@@ -1673,7 +1673,7 @@ ThereAndBack there_and_back(const DevState &s, int64_t m)
     if (most < 2 || m < 2)
         return p;
     p.unit = uneven_fours(s) ? 4 : 2;
-    const int64_t least = least_steps(s);
+    const int64_t least = std::min<int64_t>(least_steps(s), most);
     int64_t l = (m + most - 1) / most;
     l += l & 1;
     // the shortest of equal parts

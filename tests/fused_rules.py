@@ -101,6 +101,7 @@ int main(int argc, char **argv)
             ThereAndBack p = there_and_back(s, left & ~1);
             const int64_t m = p.steps;
             check(p.launches % 2 == 0 && m % 2 == 0 && m <= left, s, "there and back");
+            check(p.launches > 0 || most < 2 || left < 4 * most, s, "nothing borrowed");
             int64_t sum = 0;
             while (p.launches > 0 && sum <= left) {
                 const int steps = p.next();
